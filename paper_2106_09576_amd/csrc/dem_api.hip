@@ -125,8 +125,9 @@ struct dem_ctx {
   int* rowlen[2]{};
   int* rowcut[2]{};  // per particle: the row cuts of each list
   // displacement bound of the row cuts (StepParams::bacc, brec)
-  double* d_bacc = nullptr;
-  unsigned long long* d_brec = nullptr;
+  // and the drift log, one allocation that is read back as a whole
+  unsigned long long* d_bound = nullptr;
+  unsigned long long* h_bound = nullptr;  // pinned host copy
   uint32_t* keys = nullptr;
   int *rank = nullptr, *count = nullptr, *start = nullptr, *tile_sums = nullptr;
   int *perm0 = nullptr, *perm = nullptr, *inv = nullptr;
@@ -144,12 +145,10 @@ struct dem_ctx {
   int64_t n_rebuilds = 0;
   hipGraphExec_t graph[2][2]{};
 
-  // dynamic search trigger (rebuild_interval == 0): every force launch raises
-  // drift[slot] to its largest drift in half skins; the host keeps a bound on
-  // the largest displacement since the last search and the last step rate
+  // dynamic search trigger (rebuild_interval == 0): from the drifts of the
+  // steps (StepParams::blog, brec) the host keeps a bound on the largest
+  // displacement since the last search and the last step rate
   bool dynamic = false;
-  unsigned long long* d_drift = nullptr;  // kDynChunk + 1 records of kDriftSpread words
-  unsigned long long* h_drift = nullptr;  // pinned host copy
   double dyn_acc = 0.0;
   double dyn_rate = 0.0;
   double dyn_grav = 0.0;  // |g| dt^2 (2/skin)max: growth of the rate per step
@@ -223,9 +222,9 @@ void destroy_graphs(dem_ctx* c) {
 void free_particles(dem_ctx* c) {
   destroy_graphs(c);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
-  if (c->h_drift) {
-    (void)hipHostFree(c->h_drift);
-    c->h_drift = nullptr;
+  if (c->h_bound) {
+    (void)hipHostFree(c->h_bound);
+    c->h_bound = nullptr;
   }
   for (void* p : c->allocs) (void)hipFree(p);
   c->allocs.clear();
@@ -363,7 +362,7 @@ int enqueue_rebuild(dem_ctx* c, int check_guard, int move_forces, int64_t step_r
   return DEM_OK;
 }
 
-int enqueue_force(dem_ctx* c, int mode, int64_t step_rel, unsigned long long* drift = nullptr) {
+int enqueue_force(dem_ctx* c, int mode, int64_t step_rel) {
   const int a = c->cur, p = c->pcur;
   if (c->has_mesh)
     HIPCHK(launch_mesh(c->cfg.precision, c->sp, c->d_pw, c->d_walls, mtables(c), pbufs(c, a),
@@ -372,7 +371,7 @@ int enqueue_force(dem_ctx* c, int mode, int64_t step_rel, unsigned long long* dr
   HIPCHK(launch_force(mode, c->cfg.precision, c->sp, c->d_inst, c->d_pp, c->d_pw, c->d_walls,
                       pbufs(c, a),
                       pbufs(c, a ^ 1), c->info[p], nlist(c, p), wslots(c, p), c->F[p], c->T[p],
-                      c->d_clock, step_rel, c->d_flags, drift, c->has_mesh ? c->mtri[p] : nullptr,
+                      c->d_clock, step_rel, c->d_flags, c->has_mesh ? c->mtri[p] : nullptr,
                       c->Fm, c->Tm, c->pair_force, c->force_block, c->pair_mode, c->stream));
   c->cur ^= 1;
   return DEM_OK;
@@ -429,10 +428,10 @@ int eager_rebuild(dem_ctx* c, int64_t step_rel) {
   return timed_end(c);
 }
 
-int eager_force(dem_ctx* c, int mode, int64_t step_rel, unsigned long long* drift = nullptr) {
+int eager_force(dem_ctx* c, int mode, int64_t step_rel) {
   int rc = timed_begin(c, 0);
   if (rc) return rc;
-  rc = enqueue_force(c, mode, step_rel, drift);
+  rc = enqueue_force(c, mode, step_rel);
   if (rc) return rc;
   return timed_end(c);
 }
@@ -537,15 +536,13 @@ int launch_chunk(dem_ctx* c, int64_t clock_at_start) {
 
 int enqueue_dyn_chunk(dem_ctx* c, int L, bool search, bool last_is_call_end) {
   const int vv = c->cfg.integrator == 0;
-  HIPCHK(launch_fill_i32((int*)(c->d_drift + kDriftSpread), 0, 2 * kDriftSpread * (int64_t)L,
-                         c->stream));
   if (search) {
     int rc = enqueue_rebuild(c, 1, move_forces_at_search(c), 0);
     if (rc) return rc;
   }
   for (int j = 0; j < L; ++j) {
     const int mode = vv ? ((last_is_call_end && j == L - 1) ? 1 : 0) : 2;
-    int rc = enqueue_force(c, mode, j, c->d_drift + (size_t)kDriftSpread * (1 + j));
+    int rc = enqueue_force(c, mode, j);
     if (rc) return rc;
   }
   return DEM_OK;
@@ -603,25 +600,39 @@ int prepare_dyn_graphs(dem_ctx* c) {
   return rc;
 }
 
-// read back drift records [first, first + count) and fold them into the bound
-int fold_drift(dem_ctx* c, int first, int count) {
-  const size_t w0 = (size_t)kDriftSpread * first, nw = (size_t)kDriftSpread * count;
-  HIPCHK(hipMemcpyAsync(c->h_drift + w0, c->d_drift + w0, sizeof(unsigned long long) * nw,
+// Words of the displacement bound's allocation: bacc (3, padded to
+// kDriftStride), the drift log, the three drift records.
+constexpr int kBoundLog = kDriftStride;
+constexpr int kBoundRec = kBoundLog + kDriftLog;
+constexpr int kBoundWords = kBoundRec + 3 * kDriftRec;
+
+// Fold the drifts of the updates that produced x^first .. x^last (absolute
+// steps, at most kDynChunk of them, all enqueued) into the bound: from the log
+// where the positions' force evaluation has been enqueued (up to `evaluated`),
+// else, for the newest positions, from their record.
+int fold_drift(dem_ctx* c, int64_t first, int64_t last, int64_t evaluated) {
+  static_assert(kDynChunk < kDriftLog, "the log holds a chunk");
+  HIPCHK(hipMemcpyAsync(c->h_bound, c->d_bound, sizeof(unsigned long long) * kBoundWords,
                         hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   double rate = 0.0;
-  for (int k = first; k < first + count; ++k) {
-    double v2 = 0.0;  // the device keeps the largest square, spread over words
-    for (int w = 0; w < kDriftSpread; ++w) {
-      double x;
-      memcpy(&x, &c->h_drift[(size_t)kDriftSpread * k + w], sizeof(double));
-      v2 = std::max(v2, x);
+  for (int64_t s = first; s <= last; ++s) {
+    double v = 0.0;
+    if (s <= evaluated) {
+      memcpy(&v, &c->h_bound[kBoundLog + (s & (kDriftLog - 1))], sizeof(double));
+    } else {
+      const unsigned long long* rec = c->h_bound + kBoundRec + (s % 3) * kDriftRec;
+      for (int w = 0; w < c->sp.drift_words; ++w) {
+        double x;
+        memcpy(&x, &rec[w * kDriftStride], sizeof(double));
+        v = std::max(v, x);
+      }
+      v = std::sqrt(v);  // the device keeps the largest square
     }
-    const double v = std::sqrt(v2);
     c->dyn_acc += v;
     rate = std::max(rate, v);
   }
-  if (count > 0) c->dyn_rate = rate;
+  if (first <= last) c->dyn_rate = rate;
   return DEM_OK;
 }
 
@@ -632,11 +643,10 @@ int step_dynamic(dem_ctx* c, int64_t n_steps) {
   int rc = DEM_OK;
   if (graphs && n_steps > kDynChunk && (rc = prepare_dyn_graphs(c))) return rc;
   if (vv) {
-    HIPCHK(launch_fill_i32((int*)c->d_drift, 0, 2 * kDriftSpread, c->stream));
     HIPCHK(launch_kick_drift(c->sp, c->d_inst, pbufs(c, c->cur), c->info[c->pcur],
-                             c->F[c->pcur], c->T[c->pcur], c->d_drift, c->d_clock,
-                             s0 + 1 - c->host_base, c->stream));
-    if ((rc = fold_drift(c, 0, 1))) return rc;
+                             c->F[c->pcur], c->T[c->pcur], c->d_clock, s0 + 1 - c->host_base,
+                             c->stream));
+    if ((rc = fold_drift(c, s0 + 1, s0 + 1, s0))) return rc;
   }
   int64_t s = s0 + 1;
   while (s <= s_end) {
@@ -667,17 +677,16 @@ int step_dynamic(dem_ctx* c, int64_t n_steps) {
     } else {
       // eager: the clock stays, the step offset is explicit
       const int64_t base = (vv ? s : s - 1) - c->host_base;
-      HIPCHK(launch_fill_i32((int*)(c->d_drift + kDriftSpread), 0,
-                             2 * kDriftSpread * (int64_t)L, c->stream));
       if (search && (rc = eager_rebuild(c, base))) return rc;
       for (int j = 0; j < L; ++j) {
         const int mode = vv ? ((call_end && j == L - 1) ? 1 : 0) : 2;
-        unsigned long long* rec = c->d_drift + (size_t)kDriftSpread * (1 + j);
-        if ((rc = eager_force(c, mode, base + j, rec))) return rc;
+        if ((rc = eager_force(c, mode, base + j))) return rc;
       }
     }
-    // the last force launch of a Verlet call does not drift
-    if ((rc = fold_drift(c, 1, vv && call_end ? L - 1 : L))) return rc;
+    // the chunk evaluated the forces at x^e0 .. x^(e0 + L - 1); the last force
+    // launch of a Verlet call does not drift
+    const int64_t e0 = vv ? s : s - 1;
+    if ((rc = fold_drift(c, e0 + 1, e0 + (vv && call_end ? L - 1 : L), e0 + L - 1))) return rc;
     c->dyn_wacc += L * c->dyn_wrate;
     s += L;
   }
@@ -1149,6 +1158,11 @@ int commit(dem_ctx* c) {
   sp.rolling = c->cfg.rolling_model;
   sp.model = c->cfg.contact_model;
   sp.n_keys = (uint32_t)total_keys;
+  // about 64 wavefronts to a word (0.4 us of atomics, one after the other),
+  // one word for the smallest launches, whose lanes then read a single line
+  sp.drift_words = 1;
+  while (sp.drift_words < kDriftSpread && (int64_t)sp.drift_words * 64 * 64 < N)
+    sp.drift_words *= 2;
   sp.drift_scale = ihs_min == ihs_max ? c->cfg.dt * ihs_max : 0.0;
 
   // allocations
@@ -1188,9 +1202,7 @@ int commit(dem_ctx* c) {
   rc = rc ? rc : dalloc_t(c, &c->d_ckey, std::max<size_t>(ckey_total, 1));
   rc = rc ? rc : dalloc_t(c, &c->d_key_cell, std::max<size_t>(ckey_total, 1));
   rc = rc ? rc : dalloc_t(c, &c->d_cse, std::max<size_t>(ckey_total, 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_drift, (size_t)kDriftSpread * (kDynChunk + 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_bacc, 3);
-  rc = rc ? rc : dalloc_t(c, &c->d_brec, 3 * (size_t)kDriftSpread);
+  rc = rc ? rc : dalloc_t(c, &c->d_bound, (size_t)kBoundWords);
   if (c->record_pf)
     rc = rc ? rc : dalloc_t(c, &c->pair_force, (size_t)std::max<int64_t>(c->cap, 1) * 3);
   if (!htri.empty()) {
@@ -1206,11 +1218,10 @@ int commit(dem_ctx* c) {
     c->has_mesh = rc == DEM_OK;
   }
   if (rc == DEM_OK) {
-    hipError_t he = hipHostMalloc((void**)&c->h_drift,
-                                  sizeof(unsigned long long) * kDriftSpread * (kDynChunk + 1),
+    hipError_t he = hipHostMalloc((void**)&c->h_bound, sizeof(unsigned long long) * kBoundWords,
                                   hipHostMallocDefault);
     if (he != hipSuccess) {
-      c->h_drift = nullptr;
+      c->h_bound = nullptr;
       rc = set_err(DEM_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(he));
     }
   }
@@ -1315,10 +1326,10 @@ int commit(dem_ctx* c) {
     HIPCHK(hipMemcpyAsync(c->info[0], hinfo.data(), N * sizeof(int), hipMemcpyHostToDevice, s));
   }
   // zero-filled: forces of both parities, empty old list and wall slots
-  c->sp.bacc = c->d_bacc;
-  c->sp.brec = c->d_brec;
-  HIPCHK(launch_fill_i32((int*)c->d_bacc, 0, 6, s));
-  HIPCHK(launch_fill_i32((int*)c->d_brec, 0, 6 * kDriftSpread, s));
+  c->sp.bacc = (double*)c->d_bound;
+  c->sp.blog = (double*)(c->d_bound + kBoundLog);
+  c->sp.brec = c->d_bound + kBoundRec;
+  HIPCHK(launch_fill_i32((int*)c->d_bound, 0, 2 * kBoundWords, s));
   HIPCHK(launch_fill_i32((int*)c->F[0], 0, (int64_t)NN * 8, s));
   HIPCHK(launch_fill_i32((int*)c->T[0], 0, (int64_t)NN * 8, s));
   HIPCHK(launch_fill_i32((int*)c->F[1], 0, (int64_t)NN * 8, s));
@@ -1777,8 +1788,8 @@ int dem_step(dem_ctx* c, int64_t n_steps) {
   if (graphs && n_steps >= K && (rc = prepare_chunk_graphs(c))) return rc;
   if (c->cfg.integrator == 0) {
     HIPCHK(launch_kick_drift(c->sp, c->d_inst, pbufs(c, c->cur), c->info[c->pcur],
-                             c->F[c->pcur], c->T[c->pcur], nullptr, c->d_clock,
-                             s0 + 1 - c->host_base, c->stream));
+                             c->F[c->pcur], c->T[c->pcur], c->d_clock, s0 + 1 - c->host_base,
+                             c->stream));
     int64_t s = s0 + 1;
     while (s <= s_end) {
       if (graphs && s % K == 0 && s + K - 1 <= s_end - 1) {

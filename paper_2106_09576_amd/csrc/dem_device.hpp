@@ -16,7 +16,16 @@ constexpr int kWave = 64;
 constexpr int kTypeMask = 0xffff;
 constexpr int kInactive = 1 << 16;  // flag bit in the per-particle info word
 constexpr int kInstShift = 20;      // info bits 20..30: instance of the particle
-constexpr int kDriftSpread = 32;  // words per drift record
+// A drift record: up to kDriftSpread words (StepParams::drift_words), each
+// kDriftStride words (256 bytes) from the next.  Every wavefront of a step
+// raises one of them with an atomic.  Atomics on one cache line run one after
+// the other (about 6 ns each): with 32 words side by side on two lines, the
+// 15,648 wavefronts of a million spheres took 90 us over them, a floor under
+// every step.
+constexpr int kDriftSpread = 32;
+constexpr int kDriftStride = 32;
+constexpr int kDriftRec = kDriftSpread * kDriftStride;  // words from one record to the next
+constexpr int kDriftLog = 32;  // steps the drift log reaches back (a power of two)
 constexpr int kMaxInstances = 2048;
 constexpr int kMaxMeshTriangles = 1 << 24;  // per instance
 // Particles per context: while the contact search builds a row, the top three
@@ -135,20 +144,24 @@ struct StepParams {
   int rolling;     // 0 none, 1 constant torque, 2 viscous torque
   int model;       // 0 nonlinear (Hertz-Mindlin), 1 linear spring-dashpot
   uint32_t n_keys; // total cell keys; key n_keys collects inactive particles
+  int drift_words; // words of a drift record in use (a power of two <= kDriftSpread)
   double drift_scale;  // dt * 2 / skin when every instance has the same skin,
                        // else 0 (then taken per particle from its instance)
   // Displacement bound since the last contact search, in units of half the
   // skin of each particle's instance, for the row cuts (see NbrList): the
   // force evaluation at absolute step s (positions x^s) uses
   // acc(s) = bacc[(s - 1) % 3] + sqrt(max of brec[s % 3]), where brec[s % 3]
-  // (kDriftSpread words, non-negative doubles as bits) holds the largest
+  // (drift_words words, non-negative doubles as bits) holds the largest
   // squared drift |v| dt (half skins) of the update that produced x^s.  The
   // evaluation writes bacc[s % 3] = acc(s), raises brec[(s + 1) % 3] with
   // its own update and clears brec[(s + 2) % 3]; a search at step s sets
   // bacc[(s - 1) % 3] and brec[s % 3] to zero.  No particle has moved more
-  // than acc(s) half skins from where the last search saw it.
+  // than acc(s) half skins from where the last search saw it.  The evaluation
+  // also notes the drift of the update that produced its positions, the root
+  // of brec[s % 3], in blog[s % kDriftLog] (for the dynamic search trigger).
   double* bacc;             // 3 words
-  unsigned long long* brec; // 3 * kDriftSpread words
+  unsigned long long* brec; // 3 * kDriftRec words
+  double* blog;             // kDriftLog words
 };
 
 // Particle arrays in sorted (spatial) order.  pos = (x, y, z, R),
@@ -248,9 +261,8 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
                         const PairCoef* pw, const WallDev* walls, ParticleBufs in,
                         ParticleBufs out, const int* info, NbrList l, WallSlots ws,
                         double4* F, double4* T, const int64_t* clock, int64_t step_rel,
-                        const int* flags, unsigned long long* drift, const int* xsel,
-                        const double4* Fx, const double4* Tx, double* pf, int block,
-                        int pair_mode, hipStream_t s);
+                        const int* flags, const int* xsel, const double4* Fx, const double4* Tx,
+                        double* pf, int block, int pair_mode, hipStream_t s);
 // Contacts of the particles with triangle candidates at time (*clock +
 // step_rel) dt (tangential overlaps updated): their force and torque into
 // Fm / Tm (written for those particles only).
@@ -259,17 +271,12 @@ hipError_t launch_mesh(int precision, const StepParams& sp, const PairCoef* pw,
                        MeshSlots ms, double4* Fm, double4* Tm, const int64_t* clock,
                        int64_t step_rel, const int* flags, hipStream_t s);
 // first half kick + drift from stored forces (start of a velocity-Verlet call).
-// When drift is not null, both launchers raise the kDriftSpread words at
-// drift (as the bits of non-negative doubles) so that their maximum is the
-// largest squared drift |v| dt of the step, in units of half the particle's
-// skin (each wavefront raises one word: spreading the atomics over several
-// words keeps them from queueing on one address).
-// The kick and drift produce the positions of step *clock + step_rel, whose
-// displacement-bound record (StepParams) they raise.
+// It produces the positions of step *clock + step_rel, whose displacement-bound
+// record (StepParams) it raises to its largest squared drift |v| dt, in units
+// of half the particle's skin (each wavefront raises one word).
 hipError_t launch_kick_drift(const StepParams& sp, const InstDev* inst, ParticleBufs st,
                              const int* info, const double4* F, const double4* T,
-                             unsigned long long* drift, const int64_t* clock, int64_t step_rel,
-                             hipStream_t s);
+                             const int64_t* clock, int64_t step_rel, hipStream_t s);
 hipError_t launch_tick(int64_t* clock, int64_t k, hipStream_t s);
 // statistics: out[0] active, [1] list entries, [2] touching entries, [3] wall slots
 hipError_t launch_stats(const StepParams& sp, const double4* pos, const int* info,

@@ -494,7 +494,7 @@ __global__ void k_reorder(StepParams sp, const InstDev* __restrict__ inst,
   if (blockIdx.x == 0 && threadIdx.x < kDriftSpread) {
     // the positions of the next force evaluation are where this search sees them
     const int r = bound_slot(*clock + bound_step_rel, 0);
-    sp.brec[r * kDriftSpread + threadIdx.x] = 0ull;
+    sp.brec[r * kDriftRec + threadIdx.x * kDriftStride] = 0ull;
     if (threadIdx.x == 0) sp.bacc[bound_slot(*clock + bound_step_rel, -1)] = 0.0;
   }
   if (p >= n) return;
@@ -1438,23 +1438,48 @@ __device__ __forceinline__ double force_particle(
   return drift;
 }
 
-// Largest value of a wavefront (shuffles), then one atomic per wavefront on
-// one of kDriftSpread words: non-negative doubles order like their bit
-// patterns.  Every lane of the wavefront calls it; waves_per_block is the
-// block size in wavefronts.
-__device__ __forceinline__ void wave_max_store(unsigned long long* dst, double v,
-                                               int waves_per_block = kBlock / 64) {
-  const int w = (blockIdx.x * waves_per_block + (threadIdx.x >> 6)) & (kDriftSpread - 1);
-  if ((threadIdx.x & 63) == 0 && v > 0.0)
-    atomicMax(dst + w, (unsigned long long)__double_as_longlong(v));
+// Value of v in the lane that a DPP pattern picks (0 where it picks none): two
+// 32-bit moves, at the rate of the vector unit (a shuffle goes through LDS).
+template <int CTRL>
+__device__ __forceinline__ double dpp0(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
 }
-// returns the wavefront's maximum
-__device__ __forceinline__ double wave_max_to(unsigned long long* dst, double v,
-                                              int waves_per_block = kBlock / 64) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  wave_max_store(dst, v, waves_per_block);
+
+// Largest of a wavefront's non-negative values, in lane 63: row shifts by 1,
+// 2, 4 and 8, then the last lane of each row to the next rows.
+__device__ __forceinline__ double wave_max63(double v) {
+  v = fmax(v, dpp0<0x111>(v));
+  v = fmax(v, dpp0<0x112>(v));
+  v = fmax(v, dpp0<0x114>(v));
+  v = fmax(v, dpp0<0x118>(v));
+  v = fmax(v, dpp0<0x142>(v));
+  v = fmax(v, dpp0<0x143>(v));
   return v;
+}
+
+// Raises a drift record to the largest value of a wavefront, with one atomic
+// per wavefront: non-negative doubles order like their bit patterns.  Every
+// lane of the wavefront calls it.  Blocks go round the 8 XCDs, so a word's
+// line is mostly raised from one XCD.
+__device__ __forceinline__ void raise_drift(const StepParams& sp, unsigned long long* rec,
+                                            double v) {
+  v = wave_max63(v);
+  const int w = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & (sp.drift_words - 1);
+  if ((threadIdx.x & 63) == 63 && v > 0.0)
+    atomicMax(rec + w * kDriftStride, (unsigned long long)__double_as_longlong(v));
+}
+
+// Largest value of a drift record, the same in every lane: lane w reads word w
+// (a single load; one scalar load per word took 2 us longer in a launch of
+// few wavefronts, which nothing hides).
+__device__ __forceinline__ double drift_of(const StepParams& sp, const unsigned long long* rec) {
+  const int w = (threadIdx.x & 63) & (sp.drift_words - 1);
+  const double v = wave_max63(__longlong_as_double((long long)rec[w * kDriftStride]));
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+  return __hiloint2double(hi, lo);
 }
 
 // Occupancy floor: four wavefronts per SIMD (128 VGPRs, no spills), except
@@ -1470,9 +1495,8 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
         const PairCoef* __restrict__ pwc, const WallDev* __restrict__ walls, ParticleBufs in,
         ParticleBufs out, const int* __restrict__ info, NbrList l, WallSlots ws,
         double4* __restrict__ Fo, double4* __restrict__ To, const int64_t* __restrict__ clock,
-        int64_t step_rel, const int* __restrict__ flags, unsigned long long* __restrict__ drift,
-        const int* __restrict__ xsel, const double4* __restrict__ Fx,
-        const double4* __restrict__ Tx, double* __restrict__ pf) {
+        int64_t step_rel, const int* __restrict__ flags, const int* __restrict__ xsel,
+        const double4* __restrict__ Fx, const double4* __restrict__ Tx, double* __restrict__ pf) {
   const int b0 = xcd_block() * BS;
   const int i = b0 + threadIdx.x;
   const int64_t step = *clock + step_rel;  // these positions are x^step
@@ -1491,17 +1515,14 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
   // margin of 1e-6 covers every rounding of the bound and of the gaps)
   int u_cut;
   {
-    // the record's words, read with one address for the whole wavefront
-    // (non-negative doubles order like their bit patterns)
-    const unsigned long long* rw = sp.brec + bound_slot(step, 0) * kDriftSpread;
-    unsigned long long mb = 0ull;
-#pragma unroll
-    for (int w = 0; w < kDriftSpread; ++w) mb = rw[w] > mb ? rw[w] : mb;
-    const double m2 = __longlong_as_double((long long)mb);
-    const double acc = sp.bacc[bound_slot(step, -1)] + sqrt(m2);
+    const double m = sqrt(drift_of(sp, sp.brec + bound_slot(step, 0) * kDriftRec));
+    const double acc = sp.bacc[bound_slot(step, -1)] + m;
     if (blockIdx.x == 0 && threadIdx.x < kDriftSpread) {
-      sp.brec[bound_slot(step, 2) * kDriftSpread + threadIdx.x] = 0ull;
-      if (threadIdx.x == 0) sp.bacc[bound_slot(step, 0)] = acc;
+      sp.brec[bound_slot(step, 2) * kDriftRec + threadIdx.x * kDriftStride] = 0ull;
+      if (threadIdx.x == 0) {
+        sp.bacc[bound_slot(step, 0)] = acc;
+        sp.blog[step & (kDriftLog - 1)] = m;
+      }
     }
     const double accm = acc * (1.0 + 1e-6);
     u_cut = accm < kCutFrac[0] ? 0 : (accm < kCutFrac[1] ? 1 : (accm < kCutFrac[2] ? 2 : 3));
@@ -1519,11 +1540,8 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
     d = force_particle<R, MODE, MODEL, REC, PAIRS>(i, sp, inst, ppc, pwc, walls, in, out, info,
                                                   l, ws, Fo, To, clock, step_rel, flags,
                                                   MODE != 1, xsel, Fx, Tx, tile, len, jr0, pf);
-  if (MODE != 1) {
-    // this launch's own update produced x^(step + 1)
-    const double dm = wave_max_to(sp.brec + bound_slot(step, 1) * kDriftSpread, d, BS / 64);
-    if (drift) wave_max_store(drift, dm, BS / 64);
-  }
+  // this launch's own update produced x^(step + 1)
+  if (MODE != 1) raise_drift(sp, sp.brec + bound_slot(step, 1) * kDriftRec, d);
 }
 
 hipError_t launch_force(int mode, int precision, const StepParams& sp, const InstDev* inst,
@@ -1531,9 +1549,8 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
                         const PairCoef* pw, const WallDev* walls, ParticleBufs in,
                         ParticleBufs out, const int* info, NbrList l, WallSlots ws,
                         double4* F, double4* T, const int64_t* clock, int64_t step_rel,
-                        const int* flags, unsigned long long* drift, const int* xsel,
-                        const double4* Fx, const double4* Tx, double* pf, int block,
-                        int pair_mode, hipStream_t s) {
+                        const int* flags, const int* xsel, const double4* Fx, const double4* Tx,
+                        double* pf, int block, int pair_mode, hipStream_t s) {
   if (sp.n <= 0) return hipSuccess;
   if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
   dim3 gr(grid_for(sp.n, block)), bl(block);
@@ -1541,16 +1558,16 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
   do {                                                                                          \
     if (block == 64)                                                                            \
       hipLaunchKernelGGL((k_force<RT, M, L, 64, REC, PAIRS>), gr, bl, 0, s, sp, inst, pp, pw,   \
-                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, drift,      \
-                         xsel, Fx, Tx, pf);                                                     \
+                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, xsel, Fx,   \
+                         Tx, pf);                                                     \
     else if (block == 128)                                                                      \
       hipLaunchKernelGGL((k_force<RT, M, L, 128, REC, PAIRS>), gr, bl, 0, s, sp, inst, pp, pw,  \
-                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, drift,      \
-                         xsel, Fx, Tx, pf);                                                     \
+                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, xsel, Fx,   \
+                         Tx, pf);                                                     \
     else                                                                                        \
       hipLaunchKernelGGL((k_force<RT, M, L, 256, REC, PAIRS>), gr, bl, 0, s, sp, inst, pp, pw,  \
-                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, drift,      \
-                         xsel, Fx, Tx, pf);                                                     \
+                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, xsel, Fx,   \
+                         Tx, pf);                                                     \
   } while (0)
 #define DEM_LAUNCH(RT, M, L)                                     \
   do {                                                           \
@@ -1764,28 +1781,23 @@ __device__ __forceinline__ double kick_drift_one(int i, const StepParams& sp, co
 __global__ void k_kick_drift(StepParams sp, const InstDev* __restrict__ inst, ParticleBufs st,
                              const int* __restrict__ info, const double4* __restrict__ F,
                              const double4* __restrict__ T,
-                             unsigned long long* __restrict__ drift,
                              const int64_t* __restrict__ clock, int64_t step_rel) {
   int i = xcd_block() * kBlock + threadIdx.x;
   double d = 0.0;
   if (i < sp.n && !(info[i] & kInactive)) d = kick_drift_one(i, sp, inst, st, info, F, T, true);
   // the displacement bound's record of the update that produced x^step
   const int64_t step = *clock + step_rel;
-  const double dm = wave_max_to(sp.brec + bound_slot(step, 0) * kDriftSpread, d);
-  if (drift) wave_max_store(drift, dm);
+  raise_drift(sp, sp.brec + bound_slot(step, 0) * kDriftRec, d);
 }
 
 hipError_t launch_kick_drift(const StepParams& sp, const InstDev* inst, ParticleBufs st,
                              const int* info, const double4* F, const double4* T,
-                             unsigned long long* drift, const int64_t* clock, int64_t step_rel,
-                             hipStream_t s) {
+                             const int64_t* clock, int64_t step_rel, hipStream_t s) {
   if (sp.n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_kick_drift, dim3(grid_for(sp.n)), dim3(kBlock), 0, s, sp, inst, st, info,
-                     F, T, drift, clock, step_rel);
+                     F, T, clock, step_rel);
   return hipGetLastError();
 }
-
-
 
 __global__ void k_tick(int64_t* clock, int64_t k) {
   if (threadIdx.x == 0 && blockIdx.x == 0) clock[0] += k;
