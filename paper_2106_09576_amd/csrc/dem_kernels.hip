@@ -300,7 +300,18 @@ hipError_t launch_cell_rank(int n, int64_t n_keys, const int* perm0, const uint3
 // contact point about the wall's rotation axis (x_c - ax(t)).
 struct WallGeo {
   bool candidate, touching;
-  double n[3], dn, arm[3];
+  // scalars: as arrays filled in branches they ended up in scratch memory
+  double n0 = 0.0, n1 = 0.0, n2 = 0.0, dn = 0.0, a0 = 0.0, a1 = 0.0, a2 = 0.0;
+  __device__ __forceinline__ void set(double nx, double ny, double nz, double overlap, double ax,
+                                      double ay, double az) {
+    n0 = nx;
+    n1 = ny;
+    n2 = nz;
+    dn = overlap;
+    a0 = ax;
+    a1 = ay;
+    a2 = az;
+  }
 };
 
 __device__ inline double dot3(const double* a, const double* b) {
@@ -321,13 +332,9 @@ __device__ inline void wall_geo(const WallDev& W, const double x[3], double R, d
     }
     g.candidate = (dist < R + skin) && (dist > -R);
     g.touching = dist < R;
-    if (g.touching && need_contact) {
-      for (int k = 0; k < 3; ++k) {
-        g.n[k] = -W.nrm[k];
-        g.arm[k] = (rel[k] - dist * W.nrm[k]) - W.axo[k];
-      }
-      g.dn = R - dist;
-    }
+    if (g.touching && need_contact)
+      g.set(-W.nrm[0], -W.nrm[1], -W.nrm[2], R - dist, (rel[0] - dist * W.nrm[0]) - W.axo[0],
+            (rel[1] - dist * W.nrm[1]) - W.axo[1], (rel[2] - dist * W.nrm[2]) - W.axo[2]);
     return;
   }
   double sax = dot3(rel, W.nrm);
@@ -356,15 +363,14 @@ __device__ inline void wall_geo(const WallDev& W, const double x[3], double R, d
       g.touching = (lt > 0.0) && (rho2 < lt * lt);
     }
     if (g.touching && need_contact) {
-      double rho = sqrt(rho2);
-      double er[3] = {r[0] / rho, r[1] / rho, r[2] / rho};
-      double dist = W.inside ? (rs - rho) / q : (rho - rs) / q;
-      g.dn = R - dist;
-      for (int k = 0; k < 3; ++k) {
-        const double m = (er[k] - W.slope * W.nrm[k]) / q;
-        g.n[k] = W.inside ? m : -m;
-        g.arm[k] = (rel[k] + dist * g.n[k]) - W.axo[k];
-      }
+      const double rho = sqrt(rho2);
+      const double dist = W.inside ? (rs - rho) / q : (rho - rs) / q;
+      const double m0 = (r[0] / rho - W.slope * W.nrm[0]) / q;
+      const double m1 = (r[1] / rho - W.slope * W.nrm[1]) / q;
+      const double m2 = (r[2] / rho - W.slope * W.nrm[2]) / q;
+      const double n0 = W.inside ? m0 : -m0, n1 = W.inside ? m1 : -m1, n2 = W.inside ? m2 : -m2;
+      g.set(n0, n1, n2, R - dist, (rel[0] + dist * n0) - W.axo[0], (rel[1] + dist * n1) - W.axo[1],
+            (rel[2] + dist * n2) - W.axo[2]);
     }
     return;
   }
@@ -385,14 +391,12 @@ __device__ inline void wall_geo(const WallDev& W, const double x[3], double R, d
     g.touching = rho2 < lt * lt;
   }
   if (g.touching && need_contact) {
-    double rho = sqrt(rho2);
-    double er[3] = {r[0] / rho, r[1] / rho, r[2] / rho};
-    double dist = W.inside ? (Rc - rho) : (rho - Rc);
-    g.dn = R - dist;
-    for (int k = 0; k < 3; ++k) {
-      g.n[k] = W.inside ? er[k] : -er[k];
-      g.arm[k] = (sax * W.nrm[k] + Rc * er[k]) - W.axo[k];
-    }
+    const double rho = sqrt(rho2);
+    const double e0 = r[0] / rho, e1 = r[1] / rho, e2 = r[2] / rho;
+    const double dist = W.inside ? (Rc - rho) : (rho - Rc);
+    g.set(W.inside ? e0 : -e0, W.inside ? e1 : -e1, W.inside ? e2 : -e2, R - dist,
+          (sax * W.nrm[0] + Rc * e0) - W.axo[0], (sax * W.nrm[1] + Rc * e1) - W.axo[1],
+          (sax * W.nrm[2] + Rc * e2) - W.axo[2]);
   }
 }
 
@@ -1148,13 +1152,15 @@ __device__ __forceinline__ void pw_contact(const PairCoef& c, int rolling, int m
     Mi[0] = Mi[1] = Mi[2] = 0.0;
     return;
   }
-  wall_law<R>(c, rolling, model, dt, W, g.n, g.dn, g.arm, xi, vi, wi, dtl, Fi, Mi);
+  const double gn[3] = {g.n0, g.n1, g.n2}, arm[3] = {g.a0, g.a1, g.a2};
+  wall_law<R>(c, rolling, model, dt, W, gn, g.dn, arm, xi, vi, wi, dtl, Fi, Mi);
 }
 
 // ------------------------------------------------------------------- force
 //
-// One thread per particle walks its row in order (every load of a row entry
-// is one coalesced access for the wavefront); the neighbour's velocities and
+// A particle's lane (or its two or four lanes, see below) walks its row in
+// order, every load of a row entry one coalesced access for the wavefront; the
+// neighbour's velocities and
 // the pair history are loaded only when the pair touches.  Bit 31 of a row
 // entry marks "touching at the last evaluation" (history may be non-zero);
 // histories of other entries are zero and are neither read nor written.
@@ -1162,59 +1168,187 @@ __device__ __forceinline__ void pw_contact(const PairCoef& c, int rolling, int m
 constexpr int kTouchedBit = (int)0x80000000u;
 constexpr int kIndexMask = 0x7fffffff;
 
-// Accesses to data that only the particle's own thread touches in a force
-// launch (its row, row length, pair and wall histories, its new state) are
-// non-temporal: they are not reused from the caches within the launch, and
-// leaving L2 to the neighbour gathers, which are, made the launch 3-4 %
-// faster.
-template <typename T>
-__device__ __forceinline__ T ld_own(const T* p) {
-  return __builtin_nontemporal_load(p);
+// Value of v in the lane that a DPP pattern picks (0 where it picks none): two
+// 32-bit moves, at the rate of the vector unit (a shuffle goes through LDS).
+template <int CTRL>
+__device__ __forceinline__ double dpp0(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
 }
-template <typename T>
+
+// Largest of a wavefront's non-negative values, in lane 63: row shifts by 1,
+// 2, 4 and 8, then the last lane of each row to the next rows.
+__device__ __forceinline__ double wave_max63(double v) {
+  v = fmax(v, dpp0<0x111>(v));
+  v = fmax(v, dpp0<0x112>(v));
+  v = fmax(v, dpp0<0x114>(v));
+  v = fmax(v, dpp0<0x118>(v));
+  v = fmax(v, dpp0<0x142>(v));
+  v = fmax(v, dpp0<0x143>(v));
+  return v;
+}
+
+// Raises a drift record to the largest value of a wavefront, with one atomic
+// per wavefront: non-negative doubles order like their bit patterns.  Every
+// lane of the wavefront calls it.  Blocks go round the 8 XCDs, so a word's
+// line is mostly raised from one XCD.
+__device__ __forceinline__ void raise_drift(const StepParams& sp, unsigned long long* rec,
+                                            double v) {
+  v = wave_max63(v);
+  const int w = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & (sp.drift_words - 1);
+  if ((threadIdx.x & 63) == 63 && v > 0.0)
+    atomicMax(rec + w * kDriftStride, (unsigned long long)__double_as_longlong(v));
+}
+
+// Largest value of a drift record, the same in every lane: lane w reads word w
+// (a single load; one scalar load per word took 2 us longer in a launch of
+// few wavefronts, which nothing hides).
+__device__ __forceinline__ double drift_of(const StepParams& sp, const unsigned long long* rec) {
+  const int w = (threadIdx.x & 63) & (sp.drift_words - 1);
+  const double v = wave_max63(__longlong_as_double((long long)rec[w * kDriftStride]));
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+  return __hiloint2double(hi, lo);
+}
+
+// How a force launch shares its work among the lanes and which of its accesses
+// stream past the caches (non-temporal).  kLanes lanes work on one particle:
+// lane g takes the row's entries g, g + kLanes, ... (several entries in flight
+// where one lane would go through them one after the other), and the
+// contributions are added in row order, so the sums are the same for every
+// kLanes.  See force_way for where each is used.
+struct WaySmall4 {
+  static constexpr int kLanes = 4;
+  static constexpr bool kRowNt = false, kHistLdNt = false, kHistStNt = false, kStateNt = false;
+};
+struct WaySmall2 {
+  static constexpr int kLanes = 2;
+  static constexpr bool kRowNt = false, kHistLdNt = false, kHistStNt = false, kStateNt = false;
+};
+struct WayCached {
+  static constexpr int kLanes = 1;
+  static constexpr bool kRowNt = false, kHistLdNt = false, kHistStNt = false, kStateNt = false;
+};
+struct WayMid {
+  static constexpr int kLanes = 1;
+  static constexpr bool kRowNt = false, kHistLdNt = true, kHistStNt = true, kStateNt = false;
+};
+struct WayLarge {
+  static constexpr int kLanes = 1;
+  static constexpr bool kRowNt = true, kHistLdNt = false, kHistStNt = true, kStateNt = true;
+};
+
+template <bool NT, typename T>
+__device__ __forceinline__ T ld_own(const T* p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool NT, typename T>
 __device__ __forceinline__ void st_own(T v, T* p) {
-  __builtin_nontemporal_store(v, p);
+  if (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
 }
 typedef double own_d4 __attribute__((ext_vector_type(4)));
+template <bool NT>
 __device__ __forceinline__ void st_own(const double4& v, double4* p) {
-  const own_d4 w = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(w, reinterpret_cast<own_d4*>(p));
+  if (NT) {
+    const own_d4 w = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(w, reinterpret_cast<own_d4*>(p));
+  } else {
+    *p = v;
+  }
 }
 
-// The states of the BS consecutive sorted particles of a force block, staged
-// in LDS: in spatial (Morton) order most neighbours of a block's particles lie
-// inside the block, and they are then read from LDS instead of through the
-// cache hierarchy.
-template <int BS>
-struct Tile {
-  double4 p[BS], v[BS], w[BS];
-  int in[BS];
-  int lo, hi;  // staged particles [lo, hi)
+// acc[c] += the values v[c] of the G lanes of a particle, lane by lane: lane g
+// of the particle is lane g (64 / G) + its place in the wavefront, so whole
+// rows of 16 lanes (half rows for G = 8) are handed round.  All lanes of the
+// particle get the same sums.
+template <int G>
+__device__ __forceinline__ void add_in_order(double* acc, const double* v, int n);
 
-  __device__ __forceinline__ void stage(const ParticleBufs& src, const int* __restrict__ info,
-                                        int first, int n) {
-    const int a = first;
-    const int b = first + BS < n ? first + BS : n;
-    for (int t = threadIdx.x; t < b - a; t += BS) {
-      p[t] = src.pos[a + t];
-      v[t] = src.vel[a + t];
-      w[t] = src.omg[a + t];
-      in[t] = info[a + t];
-    }
-    if (threadIdx.x == 0) {
-      lo = a;
-      hi = b > a ? b : a;
-    }
+__device__ __forceinline__ void swap32(double v, double& x, double& y) {
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false,
+                                                  false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false,
+                                                  false);
+  x = __hiloint2double((int)h[0], (int)l[0]);
+  y = __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ void swap16(double v, double& x, double& y) {
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false,
+                                                  false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false,
+                                                  false);
+  x = __hiloint2double((int)h[0], (int)l[0]);
+  y = __hiloint2double((int)h[1], (int)l[1]);
+}
+template <>
+__device__ __forceinline__ void add_in_order<1>(double* acc, const double* v, int n) {
+#pragma unroll
+  for (int c = 0; c < n; ++c) acc[c] += v[c];
+}
+template <>
+__device__ __forceinline__ void add_in_order<2>(double* acc, const double* v, int n) {
+#pragma unroll
+  for (int c = 0; c < n; ++c) {
+    double a, b;
+    swap32(v[c], a, b);
+    acc[c] = (acc[c] + a) + b;
   }
-  __device__ __forceinline__ bool has(int j) const { return j >= lo && j < hi; }
+}
+template <>
+__device__ __forceinline__ void add_in_order<4>(double* acc, const double* v, int n) {
+#pragma unroll
+  for (int c = 0; c < n; ++c) {
+    double a, b, q[4];
+    swap32(v[c], a, b);
+    swap16(a, q[0], q[1]);
+    swap16(b, q[2], q[3]);
+    acc[c] = (((acc[c] + q[0]) + q[1]) + q[2]) + q[3];
+  }
+}
+// The states of the consecutive sorted particles of a force block, staged in
+// LDS: in spatial (Morton) order most neighbours of a block's particles lie
+// inside the block, and they are then read from LDS instead of through the
+// cache hierarchy.  One record of position, velocity and spin per particle,
+// the info words behind the records.
+template <int G>
+struct Tile {
+  double4* rec;
+  int* in;
+  int lo, cnt;  // staged particles [lo, lo + cnt)
+
+  // the lanes of a particle share the loads of its record, all of them in
+  // flight before the first is waited for
+  __device__ __forceinline__ void stage(const ParticleBufs& src, const int* __restrict__ info,
+                                        int t, int g) {
+    if (t >= cnt) return;
+    const int inf = info[lo + t];
+    if (G == 1) {
+      const double4 p = src.pos[lo + t], v = src.vel[lo + t], w = src.omg[lo + t];
+      rec[3 * t] = p;
+      rec[3 * t + 1] = v;
+      rec[3 * t + 2] = w;
+    } else {
+      const int c = G == 2 ? g : (g < 2 ? g : 2);
+      const double4* __restrict__ from = c == 0 ? src.pos : (c == 1 ? src.vel : src.omg);
+      const double4 a = from[lo + t];
+      if (G == 2 && g == 0) rec[3 * t + 2] = src.omg[lo + t];
+      rec[3 * t + c] = a;
+    }
+    if (g == 0) in[t] = inf;
+  }
+  __device__ __forceinline__ bool has(int j) const { return (unsigned)(j - lo) < (unsigned)cnt; }
   __device__ __forceinline__ double4 pos(const ParticleBufs& g, int j) const {
-    return has(j) ? p[j - lo] : g.pos[j];
+    return has(j) ? rec[3 * (j - lo)] : g.pos[j];
   }
   __device__ __forceinline__ double4 vel(const ParticleBufs& g, int j) const {
-    return has(j) ? v[j - lo] : g.vel[j];
+    return has(j) ? rec[3 * (j - lo) + 1] : g.vel[j];
   }
   __device__ __forceinline__ double4 omg(const ParticleBufs& g, int j) const {
-    return has(j) ? w[j - lo] : g.omg[j];
+    return has(j) ? rec[3 * (j - lo) + 2] : g.omg[j];
   }
   __device__ __forceinline__ int info(const int* __restrict__ g, int j) const {
     return has(j) ? in[j - lo] : g[j];
@@ -1237,9 +1371,9 @@ __device__ __forceinline__ double drift_scale(const StepParams& sp,
 // Forces on particle i and its integration; returns the squared drift of
 // this step in units of half the instance's skin (for the dynamic search
 // trigger) when asked for it.
-template <typename R, int MODE, int MODEL, bool REC, int PAIRS, typename TileT>
+template <typename R, int MODE, int MODEL, typename WAY, bool REC, int PAIRS, typename TileT>
 __device__ __forceinline__ double force_particle(
-    const int i, const StepParams& sp, const InstDev* __restrict__ inst,
+    const int i, const int g, const StepParams& sp, const InstDev* __restrict__ inst,
     const PairCoef* __restrict__ ppc, const PairCoef* __restrict__ pwc,
     const WallDev* __restrict__ walls, ParticleBufs in, ParticleBufs out,
     const int* __restrict__ info, NbrList l, WallSlots ws, double4* __restrict__ Fo,
@@ -1247,17 +1381,19 @@ __device__ __forceinline__ double force_particle(
     const int* __restrict__ flags, const bool want_drift, const int* __restrict__ xsel,
     const double4* __restrict__ Fx, const double4* __restrict__ Tx, const TileT& tile,
     const int len, const int jr0, double* __restrict__ pf) {
+  constexpr int G = WAY::kLanes;
   const int n = sp.n;
-  double4 xi = tile.pos(in, i);
   // the particle's own velocity and spin stay in the LDS tile during the row
   // walk and are read where they are used (registers for the neighbour's)
-  const int own = i - tile.lo;
-  const int inf = tile.info(info, i);
+  const int own = 3 * (i - tile.lo);
+  double4 xi = tile.rec[own];
+  const int inf = tile.in[i - tile.lo];
   // frozen after an error, and for inactive particles: carry the state over
   if ((inf & kInactive) || *flags != 0) {
+    if (g != 0) return 0.0;
     out.pos[i] = xi;
-    out.vel[i] = tile.v[own];
-    out.omg[i] = tile.w[own];
+    out.vel[i] = tile.rec[own + 1];
+    out.omg[i] = tile.rec[own + 2];
     if (MODE != 0) {
       Fo[i] = make_double4(0.0, 0.0, 0.0, 0.0);
       To[i] = make_double4(0.0, 0.0, 0.0, 0.0);
@@ -1284,101 +1420,106 @@ __device__ __forceinline__ double force_particle(
     if (uni) pc0 = ppc[rowu];
   }
   const double dt = sp.dt;
-  double F[3] = {0.0, 0.0, 0.0};
-  double T[3] = {0.0, 0.0, 0.0};
+  double FT[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // force and torque
   const int max_nb = sp.max_nb;
   const int64_t cap = l.cap;
-  // the index of entry k + 1 is loaded while entry k is worked on (the
-  // row walk is a chain of dependent loads; one index ahead costs one VGPR);
-  // the row length and entry 0 come from the caller
+  // the lane's first wall slot is loaded ahead of the row walk where there are
+  // registers for it
+  int w_next = -1;
+  if (G > 1) w_next = ws.wid[(int64_t)g * n + i];
+  // the index of the lane's next entry is loaded while its entry k is worked
+  // on (the row walk is a chain of dependent loads; one index ahead costs one
+  // VGPR); the row length and the lane's first entry come from the caller
   int jr_next = jr0;
-  for (int k = 0; k < len; ++k) {
+  for (int k0 = 0; k0 < len; k0 += G) {
+    const int k = k0 + g;
     const int64_t e = nbr_entry(i, k, max_nb);
-    const int jr = jr_next;
-    if (k + 1 < len) jr_next = ld_own(l.nbr + e + 64);  // entry (i, k + 1)
-    const int j = jr & kIndexMask;
-    // a pair touching at the last evaluation most likely still touches: its
-    // history is loaded together with the neighbour's position
-    double dtl[3] = {0.0, 0.0, 0.0};
-    if (jr & kTouchedBit) {
-      dtl[0] = ld_own(l.hist + e);
-      dtl[1] = ld_own(l.hist + cap + e);
-      dtl[2] = ld_own(l.hist + 2 * cap + e);
-    }
-    const double4 xj = tile.pos(in, j);
-    const double dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
-    const double d2 = (dx * dx + dy * dy) + dz * dz;
-    const double rsum = xi.w + xj.w;
-    if (d2 < rsum * rsum) {
-      const double4 vj = tile.vel(in, j);
-      const double4 wj = tile.omg(in, j);
-      int oi = own;
-      asm volatile("" : "+v"(oi));  // keeps the LDS reads inside the loop
-      const double4 vi = tile.v[oi];
-      const double4 wi = tile.w[oi];
-      double Fi[3], Mi[3];
-      if (PAIRS == 1) {
-        pp_contact<R>(pc0, sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, Fi, Mi);
-      } else if (PAIRS == 2) {
-        if (uni)
-          pp_contact<R>(pc0, sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, Fi, Mi);
-        else
-          pp_contact<R>(ppi[0], sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, Fi, Mi);
-      } else {
-        const int tj = tile.info(info, j) & kTypeMask;
-        pp_contact<R>(ppi[tj], sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, Fi, Mi);
+    bool touch = false;
+    double C[6];  // this lane's contact: force and torque
+    if (G > 1) C[0] = C[1] = C[2] = C[3] = C[4] = C[5] = 0.0;
+    if (G == 1 || k < len) {
+      const int jr = jr_next;
+      if (k + G < len) jr_next = ld_own<WAY::kRowNt>(l.nbr + e + 64 * G);  // entry (i, k + G)
+      const int j = jr & kIndexMask;
+      // a pair touching at the last evaluation most likely still touches: its
+      // history is loaded together with the neighbour's position
+      double dtl[3] = {0.0, 0.0, 0.0};
+      if (jr & kTouchedBit) {
+        dtl[0] = ld_own<WAY::kHistLdNt>(l.hist + e);
+        dtl[1] = ld_own<WAY::kHistLdNt>(l.hist + cap + e);
+        dtl[2] = ld_own<WAY::kHistLdNt>(l.hist + 2 * cap + e);
       }
-      st_own(dtl[0], l.hist + e);
-      st_own(dtl[1], l.hist + cap + e);
-      st_own(dtl[2], l.hist + 2 * cap + e);
-      if (!(jr & kTouchedBit)) st_own(j | kTouchedBit, l.nbr + e);
-      if (REC) {
-        pf[e] = Fi[0];
-        pf[cap + e] = Fi[1];
-        pf[2 * cap + e] = Fi[2];
+      const double4 xj = tile.pos(in, j);
+      const double dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
+      const double d2 = (dx * dx + dy * dy) + dz * dz;
+      const double rsum = xi.w + xj.w;
+      touch = d2 < rsum * rsum;
+      if (touch) {
+        const double4 vj = tile.vel(in, j);
+        const double4 wj = tile.omg(in, j);
+        int oi = own;
+        asm volatile("" : "+v"(oi));  // keeps the LDS reads inside the loop
+        const double4 vi = tile.rec[oi + 1];
+        const double4 wi = tile.rec[oi + 2];
+        if (PAIRS == 1) {
+          pp_contact<R>(pc0, sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, C, C + 3);
+        } else if (PAIRS == 2) {
+          if (uni)
+            pp_contact<R>(pc0, sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, C, C + 3);
+          else
+            pp_contact<R>(ppi[0], sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, C, C + 3);
+        } else {
+          const int tj = tile.info(info, j) & kTypeMask;
+          pp_contact<R>(ppi[tj], sp.rolling, MODEL, dt, xi, vi, wi, xj, vj, wj, dtl, C, C + 3);
+        }
+        st_own<WAY::kHistStNt>(dtl[0], l.hist + e);
+        st_own<WAY::kHistStNt>(dtl[1], l.hist + cap + e);
+        st_own<WAY::kHistStNt>(dtl[2], l.hist + 2 * cap + e);
+        if (!(jr & kTouchedBit)) st_own<WAY::kHistStNt>(j | kTouchedBit, l.nbr + e);
+        if (REC) {
+          pf[e] = C[0];
+          pf[cap + e] = C[1];
+          pf[2 * cap + e] = C[2];
+        }
+        if (G == 1) add_in_order<1>(FT, C, 6);
+      } else if (jr & kTouchedBit) {
+        st_own<WAY::kHistStNt>(0.0, l.hist + e);
+        st_own<WAY::kHistStNt>(0.0, l.hist + cap + e);
+        st_own<WAY::kHistStNt>(0.0, l.hist + 2 * cap + e);
+        st_own<WAY::kHistStNt>(j, l.nbr + e);
       }
-      F[0] += Fi[0];
-      F[1] += Fi[1];
-      F[2] += Fi[2];
-      T[0] += Mi[0];
-      T[1] += Mi[1];
-      T[2] += Mi[2];
-    } else if (jr & kTouchedBit) {
-      st_own(0.0, l.hist + e);
-      st_own(0.0, l.hist + cap + e);
-      st_own(0.0, l.hist + 2 * cap + e);
-      st_own(j, l.nbr + e);
     }
+    // adding the zeros of lanes without a contact changes no sum (one that
+    // starts at +0 never becomes -0)
+    if (G > 1 && __builtin_amdgcn_ballot_w64(touch) != 0ull) add_in_order<G>(FT, C, 6);
   }
-  double4 vi = tile.v[own];
-  double4 wi = tile.w[own];
-  // walls: time of this force evaluation
+  double4 vi = tile.rec[own + 1];
+  double4 wi = tile.rec[own + 2];
+  // walls: time of this force evaluation; lane g takes the slots g, g + G, ...
   const double t = (double)(*clock + step_rel) * dt;
-  for (int s = 0; s < kWallSlots; ++s) {
-    const int w = ws.wid[(int64_t)s * n + i];
-    if (w < 0) break;
-    const WallDev& W = walls[w];
-    double dtl[3] = {ws.hist[(int64_t)(3 * s) * n + i], ws.hist[(int64_t)(3 * s + 1) * n + i],
-                     ws.hist[(int64_t)(3 * s + 2) * n + i]};
-    double Fi[3], Mi[3];
-    if (t >= W.t_on && t < W.t_off) {
-      pw_contact<R>(pwi[W.material], sp.rolling, MODEL, dt, W, W.skin, t, xi, vi, wi, dtl, Fi,
-                    Mi);
-    } else {
-      dtl[0] = dtl[1] = dtl[2] = 0.0;
-      Fi[0] = Fi[1] = Fi[2] = 0.0;
-      Mi[0] = Mi[1] = Mi[2] = 0.0;
+#pragma unroll 1
+  for (int s0 = 0; s0 < kWallSlots; s0 += G) {
+    const int s = s0 + g;
+    const int w = G > 1 && s0 == 0 ? w_next : ws.wid[(int64_t)s * n + i];
+    if (G == 1 ? w < 0 : __builtin_amdgcn_ballot_w64(w >= 0) == 0ull) break;
+    double C[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (w >= 0) {
+      const WallDev& W = walls[w];
+      double dtl[3] = {ws.hist[(int64_t)(3 * s) * n + i], ws.hist[(int64_t)(3 * s + 1) * n + i],
+                       ws.hist[(int64_t)(3 * s + 2) * n + i]};
+      if (t >= W.t_on && t < W.t_off)
+        pw_contact<R>(pwi[W.material], sp.rolling, MODEL, dt, W, W.skin, t, xi, vi, wi, dtl, C,
+                      C + 3);
+      else
+        dtl[0] = dtl[1] = dtl[2] = 0.0;
+      st_own<WAY::kHistStNt>(dtl[0], ws.hist + (int64_t)(3 * s) * n + i);
+      st_own<WAY::kHistStNt>(dtl[1], ws.hist + (int64_t)(3 * s + 1) * n + i);
+      st_own<WAY::kHistStNt>(dtl[2], ws.hist + (int64_t)(3 * s + 2) * n + i);
     }
-    st_own(dtl[0], ws.hist + (int64_t)(3 * s) * n + i);
-    st_own(dtl[1], ws.hist + (int64_t)(3 * s + 1) * n + i);
-    st_own(dtl[2], ws.hist + (int64_t)(3 * s + 2) * n + i);
-    F[0] += Fi[0];
-    F[1] += Fi[1];
-    F[2] += Fi[2];
-    T[0] += Mi[0];
-    T[1] += Mi[1];
-    T[2] += Mi[2];
+    add_in_order<G>(FT, C, 6);
   }
+  double* F = FT;
+  double* T = FT + 3;
   if (xsel && xsel[i] >= 0) {
     const double4 fx = Fx[i], tx = Tx[i];
     F[0] += fx.x;
@@ -1428,58 +1569,14 @@ __device__ __forceinline__ double force_particle(
       if (want_drift) drift = drift2(vi, drift_scale(sp, inst, inf));
     }
   }
-  st_own(xi, out.pos + i);
-  st_own(vi, out.vel + i);
-  st_own(wi, out.omg + i);
-  if (MODE != 0) {
+  if (g == 0) st_own<WAY::kStateNt>(xi, out.pos + i);
+  if (g == 1 % G) st_own<WAY::kStateNt>(vi, out.vel + i);
+  if (g == 2 % G) st_own<WAY::kStateNt>(wi, out.omg + i);
+  if (MODE != 0 && g == 3 % G) {
     Fo[i] = make_double4(F[0], F[1], F[2], 0.0);
     To[i] = make_double4(T[0], T[1], T[2], 0.0);
   }
   return drift;
-}
-
-// Value of v in the lane that a DPP pattern picks (0 where it picks none): two
-// 32-bit moves, at the rate of the vector unit (a shuffle goes through LDS).
-template <int CTRL>
-__device__ __forceinline__ double dpp0(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-
-// Largest of a wavefront's non-negative values, in lane 63: row shifts by 1,
-// 2, 4 and 8, then the last lane of each row to the next rows.
-__device__ __forceinline__ double wave_max63(double v) {
-  v = fmax(v, dpp0<0x111>(v));
-  v = fmax(v, dpp0<0x112>(v));
-  v = fmax(v, dpp0<0x114>(v));
-  v = fmax(v, dpp0<0x118>(v));
-  v = fmax(v, dpp0<0x142>(v));
-  v = fmax(v, dpp0<0x143>(v));
-  return v;
-}
-
-// Raises a drift record to the largest value of a wavefront, with one atomic
-// per wavefront: non-negative doubles order like their bit patterns.  Every
-// lane of the wavefront calls it.  Blocks go round the 8 XCDs, so a word's
-// line is mostly raised from one XCD.
-__device__ __forceinline__ void raise_drift(const StepParams& sp, unsigned long long* rec,
-                                            double v) {
-  v = wave_max63(v);
-  const int w = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & (sp.drift_words - 1);
-  if ((threadIdx.x & 63) == 63 && v > 0.0)
-    atomicMax(rec + w * kDriftStride, (unsigned long long)__double_as_longlong(v));
-}
-
-// Largest value of a drift record, the same in every lane: lane w reads word w
-// (a single load; one scalar load per word took 2 us longer in a launch of
-// few wavefronts, which nothing hides).
-__device__ __forceinline__ double drift_of(const StepParams& sp, const unsigned long long* rec) {
-  const int w = (threadIdx.x & 63) & (sp.drift_words - 1);
-  const double v = wave_max63(__longlong_as_double((long long)rec[w * kDriftStride]));
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-  return __hiloint2double(hi, lo);
 }
 
 // Occupancy floor: four wavefronts per SIMD (128 VGPRs, no spills), except
@@ -1488,8 +1585,8 @@ __device__ __forceinline__ double drift_of(const StepParams& sp, const unsigned 
 // REC: also write every touching pair's force to pf (the per-contact record;
 // a separate instantiation, so the record costs the plain kernel nothing).
 // PAIRS: how a pair finds its material-pair constants (see force_particle).
-template <typename R, int MODE, int MODEL, int BS, bool REC, int PAIRS>
-__global__ void __launch_bounds__(BS)
+template <typename R, int MODE, int MODEL, typename WAY, bool REC, int PAIRS>
+__global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(MODE == 2 && MODEL == 1 ? 3 : 4)))
 k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restrict__ ppc,
         const PairCoef* __restrict__ pwc, const WallDev* __restrict__ walls, ParticleBufs in,
@@ -1497,17 +1594,23 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
         double4* __restrict__ Fo, double4* __restrict__ To, const int64_t* __restrict__ clock,
         int64_t step_rel, const int* __restrict__ flags, const int* __restrict__ xsel,
         const double4* __restrict__ Fx, const double4* __restrict__ Tx, double* __restrict__ pf) {
-  const int b0 = xcd_block() * BS;
-  const int i = b0 + threadIdx.x;
+  // lanes g of a particle: 64 / G lanes apart in the wavefront (see add_in_order)
+  constexpr int G = WAY::kLanes, kPerWave = 64 / G;
+  const int nb = blockDim.x / G;  // particles of the block
+  const int b0 = xcd_block() * nb;
+  const int g = G == 1 ? 0 : (threadIdx.x & 63) / kPerWave;
+  const int il = G == 1 ? threadIdx.x
+                        : (threadIdx.x >> 6) * kPerWave + (threadIdx.x & (kPerWave - 1));
+  const int i = b0 + il;
   const int64_t step = *clock + step_rel;  // these positions are x^step
-  // the row length, its cuts and the first row entry do not depend on the
-  // tile: their loads are issued before it is staged (entry 0 exists for
-  // every row)
+  // the row length, its cuts and the first row entries do not depend on the
+  // tile: their loads are issued before it is staged (the first max_nb entries
+  // exist for every row)
   int len = 0, cut = 0, jr0 = 0;
   if (i < sp.n) {
-    len = ld_own(l.rowlen + i);
-    cut = ld_own(l.rowcut + i);
-    jr0 = ld_own(l.nbr + nbr_entry(i, 0, sp.max_nb));
+    len = ld_own<WAY::kRowNt>(l.rowlen + i);
+    cut = ld_own<WAY::kRowNt>(l.rowcut + i);
+    if (g < sp.max_nb) jr0 = ld_own<WAY::kRowNt>(l.nbr + nbr_entry(i, g, sp.max_nb));
   }
   // displacement bound of x^step since the last search (half skins): the
   // previous evaluation's bound plus the largest drift of the update since;
@@ -1532,16 +1635,56 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
     const int c = (cut >> (kCutBits * u_cut)) & kCutMask;
     if (c != kCutMask && c < len) len = c;
   }
-  __shared__ Tile<BS> tile;
-  tile.stage(in, info, b0, sp.n);
+  extern __shared__ double4 force_lds[];
+  Tile<G> tile;
+  tile.rec = force_lds;
+  tile.in = reinterpret_cast<int*>(force_lds + 3 * nb);
+  tile.lo = b0;
+  tile.cnt = sp.n - b0 < nb ? sp.n - b0 : nb;
+  tile.stage(in, info, il, g);
   __syncthreads();
   double d = 0.0;
   if (i < sp.n)
-    d = force_particle<R, MODE, MODEL, REC, PAIRS>(i, sp, inst, ppc, pwc, walls, in, out, info,
+    d = force_particle<R, MODE, MODEL, WAY, REC, PAIRS>(i, g, sp, inst, ppc, pwc, walls, in, out, info,
                                                   l, ws, Fo, To, clock, step_rel, flags,
                                                   MODE != 1, xsel, Fx, Tx, tile, len, jr0, pf);
   // this launch's own update produced x^(step + 1)
   if (MODE != 1) raise_drift(sp, sp.brec + bound_slot(step, 1) * kDriftRec, d);
+}
+
+// Which way a force launch of n particles takes (us per step with an FP64 law,
+// settling beds of 1.8 touching pairs per sphere, one MI355X).
+//
+// Lanes per particle.  One lane per particle fills the chip's wavefront slots
+// (256 compute units x 16 at the kernel's registers) from 262,144 particles
+// on; below, the time is that of one particle's chain of dependent loads and
+// arithmetic, which more lanes shorten.  4 / 2 / 1 lanes: 1,000 spheres 13.6 /
+// 16.0 / 19.4; 8,000 12.5 / 15.0 / 20.2; 30,000 14.5 / 15.5 / 20.1; 50,000
+// 17.7 / 18.1 / 19.4; 60,000 in a silo 20.6 / 21.3 / 23.5; 100,000 28.0 / 23.9
+// / 25.0; 130,000 - / 27.2 / 27.5; 200,000 - / 44.6 / 41.8.  8 lanes were
+// never the best.
+//
+// Streaming.  A step touches about 400 bytes per particle (two copies of the
+// state, histories, row entries), and the memory-side cache holds 256 MB.
+// While all of it fits, nothing streams (WayCached); then the histories stream
+// past the state, which keeps fitting (WayMid); and when that does not fit
+// either, the histories are the ones to stay between their load and their
+// store (WayLarge).  Cached / mid / large: 200,000 41.8 / 46.5 / -; 300,000
+// 46.1 / 54.3 / 56.4; 600,000 91.3 / 91.4 / -; 700,000 108.6 / 99.5 / 105.6;
+// 1,000,000 149.6 / 137.8 / 145.1; 1,250,000 - / 176.7 / 175.1; 1,400,000 211 / 208 / 206; 2,000,000 286 /
+// 293 / 276; 4,300,000 in a silo 748 / 770 / 727.  (Before, every launch
+// streamed loads and stores alike: 200,000 47.1, 1,000,000 147.0, 4,300,000
+// 768.)
+constexpr int64_t kFourLanes = 50000, kTwoLanes = 120000;
+constexpr int64_t kAllCached = 600000, kStateCached = 1200000;
+
+enum { kWaySmall4, kWaySmall2, kWayCached, kWayMid, kWayLarge };
+
+static int force_way(int64_t n) {
+  if (n <= kFourLanes) return kWaySmall4;
+  if (n <= kTwoLanes) return kWaySmall2;
+  if (n <= kAllCached) return kWayCached;
+  return n <= kStateCached ? kWayMid : kWayLarge;
 }
 
 hipError_t launch_force(int mode, int precision, const StepParams& sp, const InstDev* inst,
@@ -1553,28 +1696,27 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
                         double* pf, int block, int pair_mode, hipStream_t s) {
   if (sp.n <= 0) return hipSuccess;
   if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
-  dim3 gr(grid_for(sp.n, block)), bl(block);
-#define DEM_LAUNCH_REC(RT, M, L, REC, PAIRS)                                                    \
-  do {                                                                                          \
-    if (block == 64)                                                                            \
-      hipLaunchKernelGGL((k_force<RT, M, L, 64, REC, PAIRS>), gr, bl, 0, s, sp, inst, pp, pw,   \
-                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, xsel, Fx,   \
-                         Tx, pf);                                                     \
-    else if (block == 128)                                                                      \
-      hipLaunchKernelGGL((k_force<RT, M, L, 128, REC, PAIRS>), gr, bl, 0, s, sp, inst, pp, pw,  \
-                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, xsel, Fx,   \
-                         Tx, pf);                                                     \
-    else                                                                                        \
-      hipLaunchKernelGGL((k_force<RT, M, L, 256, REC, PAIRS>), gr, bl, 0, s, sp, inst, pp, pw,  \
-                         walls, in, out, info, l, ws, F, T, clock, step_rel, flags, xsel, Fx,   \
-                         Tx, pf);                                                     \
+  const int way = pf ? kWayMid : force_way(sp.n);  // the record has one instantiation
+  const int per_block = way == kWaySmall4 ? block / 4 : (way == kWaySmall2 ? block / 2 : block);
+  const dim3 gr(grid_for(sp.n, per_block)), bl(block);
+  const size_t lds = (size_t)per_block * (3 * sizeof(double4) + sizeof(int));
+#define DEM_LAUNCH_WAY(RT, M, L, WAY, REC, PAIRS)                                                 \
+  hipLaunchKernelGGL((k_force<RT, M, L, WAY, REC, PAIRS>), gr, bl, lds, s, sp, inst, pp, pw,      \
+                     walls, in, out, info, l, ws, F, T, clock, step_rel, flags, xsel, Fx, Tx, pf)
+#define DEM_LAUNCH_PAIRS(RT, M, L, PAIRS)                                            \
+  do {                                                                               \
+    if (way == kWaySmall4) DEM_LAUNCH_WAY(RT, M, L, WaySmall4, false, PAIRS);        \
+    else if (way == kWaySmall2) DEM_LAUNCH_WAY(RT, M, L, WaySmall2, false, PAIRS);   \
+    else if (way == kWayCached) DEM_LAUNCH_WAY(RT, M, L, WayCached, false, PAIRS);   \
+    else if (way == kWayMid) DEM_LAUNCH_WAY(RT, M, L, WayMid, false, PAIRS);         \
+    else DEM_LAUNCH_WAY(RT, M, L, WayLarge, false, PAIRS);                           \
   } while (0)
-#define DEM_LAUNCH(RT, M, L)                                     \
-  do {                                                           \
-    if (pf) DEM_LAUNCH_REC(RT, M, L, true, 0);                   \
-    else if (pair_mode == 1) DEM_LAUNCH_REC(RT, M, L, false, 1); \
-    else if (pair_mode == 2) DEM_LAUNCH_REC(RT, M, L, false, 2); \
-    else DEM_LAUNCH_REC(RT, M, L, false, 0);                     \
+#define DEM_LAUNCH(RT, M, L)                                 \
+  do {                                                       \
+    if (pf) DEM_LAUNCH_WAY(RT, M, L, WayMid, true, 0);       \
+    else if (pair_mode == 1) DEM_LAUNCH_PAIRS(RT, M, L, 1);  \
+    else if (pair_mode == 2) DEM_LAUNCH_PAIRS(RT, M, L, 2);  \
+    else DEM_LAUNCH_PAIRS(RT, M, L, 0);                      \
   } while (0)
 #define DEM_LAUNCH_MODE(RT, L)                \
   do {                                        \
@@ -1591,7 +1733,8 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
   }
 #undef DEM_LAUNCH_MODE
 #undef DEM_LAUNCH
-#undef DEM_LAUNCH_REC
+#undef DEM_LAUNCH_PAIRS
+#undef DEM_LAUNCH_WAY
   return hipGetLastError();
 }
 
