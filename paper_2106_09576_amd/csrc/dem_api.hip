@@ -33,6 +33,8 @@ thread_local std::string g_err;
 constexpr double kPi = 3.14159265358979323846;
 // dynamic search: steps per chunk between two host decisions
 constexpr int kDynChunk = 16;
+// pinned staging of small readouts
+constexpr size_t kStageBytes = 256 << 10;
 
 int set_err(int code, const char* fmt, ...) {
   char buf[512];
@@ -128,6 +130,7 @@ struct dem_ctx {
   // and the drift log, one allocation that is read back as a whole
   unsigned long long* d_bound = nullptr;
   unsigned long long* h_bound = nullptr;  // pinned host copy
+  char* h_stage = nullptr;  // pinned staging of small readouts (kStageBytes, behind h_bound)
   uint32_t* keys = nullptr;
   int *rank = nullptr, *count = nullptr, *start = nullptr, *tile_sums = nullptr;
   int *perm0 = nullptr, *perm = nullptr, *inv = nullptr;
@@ -721,11 +724,11 @@ int flags_to_error(dem_ctx* c, int flags) {
 
 // host copy of the current particle arrays in sorted order
 struct HostSnapshot {
-  std::vector<double4> pos, vel, omg;
+  std::vector<double4> pos;
   std::vector<int> gid, info;
 };
 
-int snapshot(dem_ctx* c, HostSnapshot& h, bool want_pos, bool want_vel, bool want_omg) {
+int snapshot(dem_ctx* c, HostSnapshot& h, bool want_pos) {
   const size_t n = (size_t)c->n;
   h.gid.resize(n);
   h.info.resize(n);
@@ -738,18 +741,88 @@ int snapshot(dem_ctx* c, HostSnapshot& h, bool want_pos, bool want_vel, bool wan
     HIPCHK(hipMemcpyAsync(h.pos.data(), c->pos[c->cur], n * sizeof(double4),
                           hipMemcpyDeviceToHost, c->stream));
   }
-  if (want_vel) {
-    h.vel.resize(n);
-    HIPCHK(hipMemcpyAsync(h.vel.data(), c->vel[c->cur], n * sizeof(double4),
-                          hipMemcpyDeviceToHost, c->stream));
-  }
-  if (want_omg) {
-    h.omg.resize(n);
-    HIPCHK(hipMemcpyAsync(h.omg.data(), c->omg[c->cur], n * sizeof(double4),
-                          hipMemcpyDeviceToHost, c->stream));
-  }
   HIPCHK(hipStreamSynchronize(c->stream));
   return DEM_OK;
+}
+
+// Current device for the span of a call: the context's, so that its kernels
+// can be launched whatever device the caller has current.
+struct DeviceScope {
+  int prev = -1;
+  explicit DeviceScope(int dev) {
+    int now = -1;
+    if (hipGetDevice(&now) == hipSuccess && now != dev && hipSetDevice(dev) == hipSuccess)
+      prev = now;
+  }
+  ~DeviceScope() {
+    if (prev >= 0) (void)hipSetDevice(prev);
+  }
+};
+
+// Whether kernels of the context's device can write `bytes` at p: inside one
+// allocation of that device, aligned.
+bool kernel_can_write(const dem_ctx* c, const void* p, size_t bytes, uintptr_t align) {
+  if ((uintptr_t)p % align != 0) return false;
+  hipPointerAttribute_t a;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice ||
+      a.device != c->device ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return (const char*)p + bytes <= (const char*)base + size;
+}
+
+// Rows of an instance's particles in input order, into device memory: at most
+// three vector arrays (sorted order) and the active flags.  Works in c->rank,
+// which only a contact search uses otherwise.
+int rows_to_device(dem_ctx* c, int32_t instance, const RowsOut& r) {
+  const Instance& I = c->inst[(size_t)instance];
+  HIPCHK(launch_place(c->n, instance, (int)I.p_begin, c->info[c->pcur], c->gid[c->pcur], c->rank,
+                      c->stream));
+  HIPCHK(launch_rows_out(I.n, c->rank, r, c->info[c->pcur], c->stream));
+  return DEM_OK;
+}
+
+// The same into host arrays (any of them null).  Up to kStageBytes of results
+// are written by the kernel into pinned memory and copied from there; larger
+// ones go through the copy of the state that the next step overwrites (the
+// other half of the ping-pong buffers) and the runtime's copies.
+int rows_to_host(dem_ctx* c, int32_t instance, const double4* const src[3], double* const out[3],
+                 uint8_t* active) {
+  const size_t n = (size_t)c->inst[(size_t)instance].n;
+  size_t bytes = 0;
+  for (int a = 0; a < 3; ++a) bytes += out[a] ? 24 * n : 0;
+  bytes += active ? n : 0;
+  if (n == 0 || bytes == 0) return finish(c);
+  const DeviceScope on(c->device);
+  RowsOut r{};
+  double* const other[3] = {(double*)c->pos[c->cur ^ 1], (double*)c->vel[c->cur ^ 1],
+                            (double*)c->omg[c->cur ^ 1]};
+  const bool staged = bytes <= kStageBytes;
+  char* at = c->h_stage;
+  for (int a = 0; a < 3; ++a) {
+    if (!out[a]) continue;
+    r.src[a] = src[a];
+    r.out[a] = staged ? (double*)at : other[a];
+    at += 24 * n;
+  }
+  if (active) r.active = staged ? (uint8_t*)at : (uint8_t*)c->keys;
+  if (int rc = rows_to_device(c, instance, r)) return rc;
+  if (staged) {
+    if (int rc = finish(c)) return rc;
+    for (int a = 0; a < 3; ++a)
+      if (out[a]) memcpy(out[a], r.out[a], 24 * n);
+    if (active) memcpy(active, r.active, n);
+    return DEM_OK;
+  }
+  for (int a = 0; a < 3; ++a)
+    if (out[a])
+      HIPCHK(hipMemcpyAsync(out[a], r.out[a], 24 * n, hipMemcpyDeviceToHost, c->stream));
+  if (active) HIPCHK(hipMemcpyAsync(active, r.active, n, hipMemcpyDeviceToHost, c->stream));
+  return finish(c);
 }
 
 int commit(dem_ctx* c);
@@ -1218,11 +1291,14 @@ int commit(dem_ctx* c) {
     c->has_mesh = rc == DEM_OK;
   }
   if (rc == DEM_OK) {
-    hipError_t he = hipHostMalloc((void**)&c->h_bound, sizeof(unsigned long long) * kBoundWords,
+    hipError_t he = hipHostMalloc((void**)&c->h_bound,
+                                  sizeof(unsigned long long) * kBoundWords + kStageBytes,
                                   hipHostMallocDefault);
     if (he != hipSuccess) {
       c->h_bound = nullptr;
       rc = set_err(DEM_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(he));
+    } else {
+      c->h_stage = (char*)(c->h_bound + kBoundWords);
     }
   }
   if (rc) {
@@ -1614,7 +1690,7 @@ int dem_get_mesh_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* tr
   }
   if (int rc = wait_user(c)) return rc;
   HostSnapshot h;
-  if (int rc = snapshot(c, h, false, false, false)) return rc;
+  if (int rc = snapshot(c, h, false)) return rc;
   const size_t n = (size_t)c->n;
   std::vector<int> tr(n * kMeshSlots);
   std::vector<double> th(n * kMeshSlots * 3);
@@ -1826,29 +1902,9 @@ int dem_get_state(dem_ctx* c, int32_t instance, double* pos, double* vel, double
   if (int rc = require_ready(c)) return rc;
   if (int rc = check_instance(c, instance)) return rc;
   if (int rc = wait_user(c)) return rc;
-  HostSnapshot h;
-  if (int rc = snapshot(c, h, pos != nullptr, vel != nullptr, omega != nullptr)) return rc;
-  const int64_t base = c->inst[(size_t)instance].p_begin;
-  for (int p = 0; p < c->n; ++p) {
-    if ((h.info[p] >> kInstShift) != instance) continue;
-    const int64_t g = h.gid[p] - base;
-    if (pos) {
-      pos[3 * g] = h.pos[p].x;
-      pos[3 * g + 1] = h.pos[p].y;
-      pos[3 * g + 2] = h.pos[p].z;
-    }
-    if (vel) {
-      vel[3 * g] = h.vel[p].x;
-      vel[3 * g + 1] = h.vel[p].y;
-      vel[3 * g + 2] = h.vel[p].z;
-    }
-    if (omega) {
-      omega[3 * g] = h.omg[p].x;
-      omega[3 * g + 1] = h.omg[p].y;
-      omega[3 * g + 2] = h.omg[p].z;
-    }
-    if (active) active[g] = (h.info[p] & kInactive) ? 0 : 1;
-  }
+  const double4* const src[3] = {c->pos[c->cur], c->vel[c->cur], c->omg[c->cur]};
+  double* const out[3] = {pos, vel, omega};
+  if (int rc = rows_to_host(c, instance, src, out, active)) return rc;
   if (time_out) *time_out = (double)c->step * c->cfg.dt;
   return DEM_OK;
 }
@@ -1858,6 +1914,17 @@ int dem_get_state_device(dem_ctx* c, int32_t instance, double* pos, double* vel,
   if (int rc = require_ready(c)) return rc;
   if (int rc = check_instance(c, instance)) return rc;
   const size_t n = (size_t)c->inst[(size_t)instance].n;
+  bool direct = n > 0;
+  for (const double* p : {pos, vel, omega})
+    direct = direct && (!p || kernel_can_write(c, p, 24 * n, 8));
+  if (direct && (!active || kernel_can_write(c, active, n, 1))) {
+    if (int rc = wait_user(c)) return rc;
+    const DeviceScope on(c->device);
+    RowsOut r{{c->pos[c->cur], c->vel[c->cur], c->omg[c->cur]}, {pos, vel, omega}, active};
+    if (int rc = rows_to_device(c, instance, r)) return rc;
+    return finish(c);
+  }
+  // memory that the context's kernels cannot write (another device's): copies
   std::vector<double> p(pos ? 3 * n : 0), v(vel ? 3 * n : 0), w(omega ? 3 * n : 0);
   std::vector<uint8_t> a(active ? n : 0);
   int rc = dem_get_state(c, instance, pos ? p.data() : nullptr, vel ? v.data() : nullptr,
@@ -1874,33 +1941,9 @@ int dem_get_forces(dem_ctx* c, int32_t instance, double* force, double* torque) 
   if (int rc = require_ready(c)) return rc;
   if (int rc = check_instance(c, instance)) return rc;
   if (int rc = wait_user(c)) return rc;
-  HostSnapshot h;
-  if (int rc = snapshot(c, h, false, false, false)) return rc;
-  const size_t n = (size_t)c->n;
-  std::vector<double4> F(n), T(n);
-  if (n > 0) {
-    HIPCHK(hipMemcpyAsync(F.data(), c->F[c->pcur], n * sizeof(double4), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(T.data(), c->T[c->pcur], n * sizeof(double4), hipMemcpyDeviceToHost,
-                          c->stream));
-  }
-  if (int rc = finish(c)) return rc;
-  const int64_t base = c->inst[(size_t)instance].p_begin;
-  for (size_t p = 0; p < n; ++p) {
-    if ((h.info[p] >> kInstShift) != instance) continue;
-    const int64_t g = h.gid[p] - base;
-    if (force) {
-      force[3 * g] = F[p].x;
-      force[3 * g + 1] = F[p].y;
-      force[3 * g + 2] = F[p].z;
-    }
-    if (torque) {
-      torque[3 * g] = T[p].x;
-      torque[3 * g + 1] = T[p].y;
-      torque[3 * g + 2] = T[p].z;
-    }
-  }
-  return DEM_OK;
+  const double4* const src[3] = {c->F[c->pcur], c->T[c->pcur], nullptr};
+  double* const out[3] = {force, torque, nullptr};
+  return rows_to_host(c, instance, src, out, nullptr);
 }
 
 int dem_get_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* pairs, double* delta_t,
@@ -1910,7 +1953,7 @@ int dem_get_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* pairs, 
   if (cap < 0) return set_err(DEM_EINVAL, "cap must be >= 0");
   if (int rc = wait_user(c)) return rc;
   HostSnapshot h;
-  if (int rc = snapshot(c, h, true, false, false)) return rc;
+  if (int rc = snapshot(c, h, true)) return rc;
   const size_t n = (size_t)c->n;
   std::vector<int> rl(n), nb((size_t)c->cap);
   std::vector<double> hs((size_t)c->cap * 3);
@@ -1996,7 +2039,7 @@ int dem_restore(dem_ctx* c, int32_t instance, int64_t n_pairs, const int64_t* pa
     }
   }
   HostSnapshot h;
-  if (int rc = snapshot(c, h, true, false, false)) return rc;
+  if (int rc = snapshot(c, h, true)) return rc;
   const size_t n = (size_t)c->n;
   const int L = c->pcur;
   const Instance& In = c->inst[(size_t)instance];
@@ -2119,7 +2162,7 @@ int dem_restore_mesh_contacts(dem_ctx* c, int32_t instance, int64_t n_tri,
   }
   if (int rc = wait_user(c)) return rc;
   HostSnapshot h;
-  if (int rc = snapshot(c, h, true, false, false)) return rc;
+  if (int rc = snapshot(c, h, true)) return rc;
   const size_t n = (size_t)c->n;
   const int L = c->pcur;
   const Instance& In = c->inst[(size_t)instance];
@@ -2315,7 +2358,7 @@ int dem_get_contact_forces(dem_ctx* c, int32_t instance, int64_t cap, int64_t* p
                    "belongs to the previous contact list");
   if (int rc = wait_user(c)) return rc;
   HostSnapshot h;
-  if (int rc = snapshot(c, h, false, false, false)) return rc;
+  if (int rc = snapshot(c, h, false)) return rc;
   const size_t n = (size_t)c->n;
   std::vector<int> rl(n), nb((size_t)c->cap);
   std::vector<double> pf((size_t)c->cap * 3);
@@ -2374,7 +2417,7 @@ int dem_get_wall_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* pa
   if (cap < 0) return set_err(DEM_EINVAL, "cap must be >= 0");
   if (int rc = wait_user(c)) return rc;
   HostSnapshot h;
-  if (int rc = snapshot(c, h, false, false, false)) return rc;
+  if (int rc = snapshot(c, h, false)) return rc;
   const size_t n = (size_t)c->n;
   std::vector<int> w(n * kWallSlots);
   std::vector<double> wh(n * kWallSlots * 3);

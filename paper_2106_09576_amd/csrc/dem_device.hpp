@@ -282,6 +282,20 @@ hipError_t launch_tick(int64_t* clock, int64_t k, hipStream_t s);
 hipError_t launch_stats(const StepParams& sp, const double4* pos, const int* info,
                         NbrList l, WallSlots ws, unsigned long long* out, hipStream_t s);
 
+// Readout in input order.  launch_place: at[gid - gid_base] = sorted index, for
+// the particles of instance inst.  launch_rows_out: the first three components
+// of row at[g] of each given array (null: skipped) to out[3 g ..], g < n, and
+// the active flag to active[g] (null: skipped).
+struct RowsOut {
+  const double4* src[3];
+  double* out[3];
+  uint8_t* active;
+};
+hipError_t launch_place(int n_all, int inst, int gid_base, const int* info, const int* gid,
+                        int* at, hipStream_t s);
+hipError_t launch_rows_out(int64_t n, const int* at, const RowsOut& r, const int* info,
+                           hipStream_t s);
+
 // Candidate pairs of instance inst on the device (see dem_get_contacts_device).
 // scratch holds pairs_scratch_ints(sp.n) ints: block counts, their exclusive
 // scan (scratch[nb + nb] is the total afterwards) and the scan's tile sums.
