@@ -102,6 +102,9 @@ struct dem_ctx {
   double cell_factor = 0.0;  // cell edge / d_max of the grids in use
   uint32_t* d_ckey = nullptr;  // cell keys of every grid (GridDev::ckey)
   uint32_t* d_key_cell = nullptr;  // inverse: the cell (key_base + position) of each key
+  SearchBlock* d_blocks = nullptr;  // search blocks of every grid
+  int* d_occupied = nullptr;  // list of occupied search blocks (scratch of a search)
+  int n_blocks = 0;
   int2* d_cse = nullptr;  // (start, end) of each cell at its position, written by the scan
   double4 *pos[2]{}, *vel[2]{}, *omg[2]{};
   int *gid[2]{}, *info[2]{};
@@ -236,6 +239,8 @@ void free_particles(dem_ctx* c) {
   c->d_ckey = nullptr;
   c->d_key_cell = nullptr;
   c->d_cse = nullptr;
+  c->d_blocks = nullptr;
+  c->d_occupied = nullptr;
   c->has_mesh = false;
   c->d_tri = nullptr;
   c->d_mcell = c->d_mcell_tri = nullptr;
@@ -357,8 +362,9 @@ int enqueue_rebuild(dem_ctx* c, int check_guard, int move_forces, int64_t step_r
                         move_forces ? c->F[p] : nullptr,
                         move_forces ? c->T[p] : nullptr, c->F[p ^ 1], c->T[p ^ 1],
                         c->d_clock, step_rel, bound_step_rel, c->d_flags, s));
-  HIPCHK(launch_search(c->d_inst, (int)c->inst.size(), c->sp, c->pos[a ^ 1], c->info[p ^ 1],
-                       c->d_cse, c->perm, c->inv, nlist(c, p), nlist(c, p ^ 1), c->d_flags, s));
+  HIPCHK(launch_search(c->d_inst, c->sp, c->d_blocks, c->n_blocks, c->d_occupied, c->pos[a ^ 1],
+                       c->info[p ^ 1], c->d_cse, c->start, c->perm, c->inv, nlist(c, p), nlist(c, p ^ 1),
+                       c->d_flags, s));
   c->cur ^= 1;
   c->pcur ^= 1;
   c->n_rebuilds += 1;
@@ -1011,17 +1017,48 @@ int plan_grids(dem_ctx* c, double cf, int64_t* total_keys_out, size_t* ckey_tota
   return DEM_OK;
 }
 
+// Cells to a search block: the largest block whose region (one layer of cells
+// more on every side) still fits the search's LDS stage in a bed at packing
+// fraction 0.6, from the mean particle volume and the cell volume.  Equal
+// spheres of diameter d with cells of 1.3 d have 2.5 particles to a cell: 4 x 4
+// x 4 cells, 540 particles to a region; log-normal spheres of 2 to 3.5 mm have
+// 6.7: 4 x 4 x 2 cells, 960 to a region.
+void plan_search_blocks(dem_ctx* c) {
+  double per_cell = 0.0, row = 0.0;
+  for (const Instance& I : c->inst) {
+    double vol = 0.0;
+    for (double r : I.rad) vol += 4.0 / 3.0 * kPi * r * r * r;
+    if (I.n == 0) continue;
+    per_cell = std::max(per_cell, 0.6 * I.h * I.h * I.h * (double)I.n / vol);
+    row = std::max(row, 0.6 * 4.0 / 3.0 * kPi * I.rs * I.rs * I.rs * (double)I.n / vol);
+  }
+  // what is kept in LDS per particle, from the mean row of such a bed: lists of
+  // 2 bytes an entry that nearly every particle's candidates fit in (those of
+  // the others are found a slower way), rows of 4 bytes an entry that may spill
+  // a little
+  c->sp.list_cap = std::min((int)(1.5 * row) + 1, 88);
+  c->sp.row_cap = std::min({(int)(1.2 * row) + 2, 48, c->max_nb});
+  const int shapes[4][3] = {{2, 2, 2}, {2, 2, 1}, {2, 1, 1}, {1, 1, 1}};
+  for (const auto& s : shapes) {
+    for (int a = 0; a < 3; ++a) c->sp.sb_bits[a] = s[a];
+    if (per_cell * ((1 << s[0]) + 2) * ((1 << s[1]) + 2) * ((1 << s[2]) + 2) <= kSearchRegion)
+      break;
+  }
+}
+
 // Cell-key tables of the instance grids and the instance table.  A cell's
 // Morton code interleaves the bits of its coordinates (bit l of axis a goes
 // to the next free code bit, levels l = 0, 1, ... and axes x, y, z in turn,
 // an axis dropping out once its bits are used up); its key is its rank by
 // that code among the grid's cells.  The tables live at c->d_ckey; hkeycell
 // (at c->d_key_cell) is the inverse, key -> cell, both over all instances.
+// hblocks: the search blocks (StepParams::sb_bits) of every grid, in key order.
 void grid_tables(dem_ctx* c, std::vector<uint32_t>* hckey, std::vector<uint32_t>* hkeycell,
-                 std::vector<InstDev>* hinst) {
+                 std::vector<InstDev>* hinst, std::vector<SearchBlock>* hblocks) {
   const int B = (int)c->inst.size();
   hckey->clear();
   hkeycell->clear();
+  hblocks->clear();
   hinst->assign((size_t)B, InstDev{});
   std::vector<std::pair<uint64_t, uint32_t>> code;
   for (int b = 0; b < B; ++b) {
@@ -1061,9 +1098,18 @@ void grid_tables(dem_ctx* c, std::vector<uint32_t>* hckey, std::vector<uint32_t>
     std::sort(code.begin(), code.end());
     hckey->resize(base + cells);
     hkeycell->resize(base + cells);
+    // a search block's cells share all but the lowest code bits
+    int low = 0;
+    for (int a = 0; a < 3; ++a) low += std::min(bits[a], c->sp.sb_bits[a]);
     for (size_t r = 0; r < cells; ++r) {
-      (*hckey)[base + code[r].second] = (uint32_t)r;
-      (*hkeycell)[base + r] = (uint32_t)(base + code[r].second);
+      const uint32_t lin = code[r].second;
+      (*hckey)[base + lin] = (uint32_t)r;
+      (*hkeycell)[base + r] = (uint32_t)(base + lin);
+      if (r == 0 || (code[r].first >> low) != (code[r - 1].first >> low))
+        hblocks->push_back(SearchBlock{I.key_base + (uint32_t)r, 0, b, (int)(lin % (uint32_t)g.nc[0]),
+                                       (int)(lin / (uint32_t)g.nc[0] % (uint32_t)g.nc[1]),
+                                       (int)(lin / (uint32_t)g.nc[0] / (uint32_t)g.nc[1])});
+      hblocks->back().ncell += 1;
     }
     g.ckey = c->d_ckey + base;
     InstDev& D = (*hinst)[(size_t)b];
@@ -1076,6 +1122,12 @@ void grid_tables(dem_ctx* c, std::vector<uint32_t>* hckey, std::vector<uint32_t>
     D.guard2 = (0.5 * I.skin) * (0.5 * I.skin);
     D.skin = I.skin;
     D.ihs = I.skin > 0.0 ? 2.0 / I.skin : 0.0;
+    // FP32 pretest of the search, in cell edges: coordinates below 8 are rounded
+    // to 2^-22, differences and their squares add a few 2^-24 of themselves; a
+    // pair at distance d < 1 is thus at most 2 sqrt(3) d 2^-21 + 2^-21 d^2 off
+    // in d^2, below 4e-6
+    D.ih = 1.0 / g.h;
+    D.near2 = (float)(I.rs * I.rs * D.ih * D.ih + 4e-6) * 1.000001f;
   }
 }
 
@@ -1095,6 +1147,10 @@ int regrid(dem_ctx* c, double cf) {
   dfree(c, c->d_ckey);
   dfree(c, c->d_key_cell);
   dfree(c, c->d_cse);
+  dfree(c, c->d_blocks);
+  dfree(c, c->d_occupied);
+  c->d_blocks = nullptr;
+  c->d_occupied = nullptr;
   c->count = c->start = c->tile_sums = nullptr;
   c->d_ckey = c->d_key_cell = nullptr;
   c->d_cse = nullptr;
@@ -1110,8 +1166,19 @@ int regrid(dem_ctx* c, double cf) {
   }
   std::vector<uint32_t> hckey, hkeycell;
   std::vector<InstDev> hinst;
-  grid_tables(c, &hckey, &hkeycell, &hinst);
+  std::vector<SearchBlock> hblocks;
+  plan_search_blocks(c);
+  grid_tables(c, &hckey, &hkeycell, &hinst, &hblocks);
+  c->n_blocks = (int)hblocks.size();
+  rc = dalloc_t(c, &c->d_blocks, std::max<size_t>(hblocks.size(), 1));
+  rc = rc ? rc : dalloc_t(c, &c->d_occupied, hblocks.size() + 1);
+  if (rc) {
+    c->failed = true;
+    return rc;
+  }
   if (!hckey.empty()) {
+    HIPCHK(hipMemcpyAsync(c->d_blocks, hblocks.data(), hblocks.size() * sizeof(SearchBlock),
+                          hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->d_ckey, hckey.data(), hckey.size() * sizeof(uint32_t),
                           hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->d_key_cell, hkeycell.data(), hkeycell.size() * sizeof(uint32_t),
@@ -1309,7 +1376,16 @@ int commit(dem_ctx* c) {
   // cell-key tables, instance table, walls and material-pair tables
   std::vector<uint32_t> hckey, hkeycell;
   std::vector<InstDev> hinst;
-  grid_tables(c, &hckey, &hkeycell, &hinst);
+  std::vector<SearchBlock> hblocks;
+  plan_search_blocks(c);
+  grid_tables(c, &hckey, &hkeycell, &hinst, &hblocks);
+  c->n_blocks = (int)hblocks.size();
+  rc = dalloc_t(c, &c->d_blocks, std::max<size_t>(hblocks.size(), 1));
+  rc = rc ? rc : dalloc_t(c, &c->d_occupied, hblocks.size() + 1);
+  if (rc) {
+    free_particles(c);
+    return rc;
+  }
   std::vector<WallDev> hwalls;
   std::vector<PairCoef> pp((size_t)B * kMaxTypes * kMaxTypes), pw(pp.size());
   memset(pp.data(), 0, pp.size() * sizeof(PairCoef));
@@ -1372,6 +1448,8 @@ int commit(dem_ctx* c) {
     HIPCHK(hipMemcpyAsync(c->d_ckey, hckey.data(), hckey.size() * sizeof(uint32_t),
                           hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(c->d_key_cell, hkeycell.data(), hkeycell.size() * sizeof(uint32_t),
+                          hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(c->d_blocks, hblocks.data(), hblocks.size() * sizeof(SearchBlock),
                           hipMemcpyHostToDevice, s));
   }
   HIPCHK(hipMemcpyAsync(c->d_inst, hinst.data(), hinst.size() * sizeof(InstDev),

@@ -122,6 +122,17 @@ struct GridDev {
   int64_t n_keys;  // nc[0] * nc[1] * nc[2]
 };
 
+// A block of neighbouring cells that a workgroup of the contact search works
+// on: the cells of an instance whose coordinates agree above the low
+// StepParams::sb_bits bits.  Its cells are consecutive in Morton order, so its
+// particles are consecutive too: the keys [key, key + ncell); (x, y, z) is its
+// first cell.
+constexpr int kSearchRegion = 1024;  // particles that its LDS stage holds
+struct SearchBlock {
+  uint32_t key;
+  int ncell, inst, x, y, z;
+};
+
 // One independent simulation of a batch.  Its cells use the global keys
 // [key_base, key_base + grid.n_keys); its walls are walls[wall_begin,
 // wall_end); its material-pair constants start at coef_base in the tables.
@@ -134,6 +145,8 @@ struct InstDev {
   double guard2;  // (skin/2)^2
   double skin;    // r_s - d_max
   double ihs;     // 2 / skin (drift in units of half the skin)
+  double ih;      // 1 / cell edge
+  float near2;    // (r_s / cell edge)^2 with a margin for the search's FP32 pretest
 };
 
 struct StepParams {
@@ -144,6 +157,9 @@ struct StepParams {
   int rolling;     // 0 none, 1 constant torque, 2 viscous torque
   int model;       // 0 nonlinear (Hertz-Mindlin), 1 linear spring-dashpot
   uint32_t n_keys; // total cell keys; key n_keys collects inactive particles
+  int sb_bits[3];  // search block: 2^sb_bits cells along each axis
+  int list_cap;    // candidates past the search's pretest kept per particle in LDS
+  int row_cap;     // entries of a row sorted in LDS
   int drift_words; // words of a drift record in use (a power of two <= kDriftSpread)
   double drift_scale;  // dt * 2 / skin when every instance has the same skin,
                        // else 0 (then taken per particle from its instance)
@@ -238,11 +254,13 @@ hipError_t launch_reorder(const StepParams& sp, const InstDev* inst, const int* 
                           double4* T_dst, const int64_t* clock, int64_t step_rel,
                           int64_t bound_step_rel, int* flags, hipStream_t s);
 // cse: (start, end) of every cell in sorted order, indexed by the cell's
-// position (key_base + (cz * nc[1] + cy) * nc[0] + cx)
-hipError_t launch_search(const InstDev* inst, int n_inst, const StepParams& sp,
-                         const double4* pos, const int* info, const int2* cse, const int* perm,
-                         const int* inv, NbrList old_l, NbrList new_l, int* flags,
-                         hipStream_t s);
+// position (key_base + (cz * nc[1] + cy) * nc[0] + cx); start: of every key;
+// blocks: the search blocks of all instances in key order; occupied: n_blocks +
+// 1 words of scratch
+hipError_t launch_search(const InstDev* inst, const StepParams& sp, const SearchBlock* blocks,
+                         int n_blocks, int* occupied, const double4* pos, const int* info,
+                         const int2* cse, const int* start, const int* perm, const int* inv,
+                         NbrList old_l, NbrList new_l, int* flags, hipStream_t s);
 
 // force + integration kernels.  mode: 0 = velocity Verlet fused (second half
 // kick of this step, first half kick and drift of the next), 1 = velocity
