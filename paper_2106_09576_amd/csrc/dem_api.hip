@@ -831,6 +831,112 @@ int rows_to_host(dem_ctx* c, int32_t instance, const double4* const src[3], doub
   return finish(c);
 }
 
+// Contact lists in input order.  They are put together in memory that is free
+// between steps: the counts and their scan in the other half of the position
+// buffers (32 bytes per particle), the results in the pinned staging when they
+// are small, else in the histories of the other list, which the next search
+// overwrites (24 bytes for every entry, and two entries make one pair of at
+// most 41 bytes; only wall contacts of a context with very few neighbours per
+// particle may need memory of their own).
+struct ContactsOut {
+  int64_t* pairs = nullptr;
+  double* values = nullptr;
+  uint8_t* touching = nullptr;
+  bool staged = false;
+  void* temp = nullptr;
+  ContactsOut() = default;
+  ContactsOut(const ContactsOut&) = delete;
+  ContactsOut& operator=(const ContactsOut&) = delete;
+  ~ContactsOut() {
+    if (temp) (void)hipFree(temp);
+  }
+};
+
+int* contact_scratch(dem_ctx* c) { return (int*)c->pos[c->cur ^ 1]; }
+
+int contacts_out(dem_ctx* c, int64_t total, bool pairs, bool values, bool touching,
+                 ContactsOut* o) {
+  const size_t bytes = (size_t)total * ((pairs ? 16 : 0) + (values ? 24 : 0) + (touching ? 1 : 0));
+  o->staged = bytes <= kStageBytes;
+  char* at = o->staged ? c->h_stage : (char*)c->hist[c->pcur ^ 1];
+  if (!o->staged && bytes > 24 * (size_t)c->cap) {
+    const hipError_t e = hipMalloc(&o->temp, bytes);
+    if (e != hipSuccess) {
+      o->temp = nullptr;
+      return set_err(DEM_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
+    }
+    at = (char*)o->temp;
+  }
+  if (pairs) {
+    o->pairs = (int64_t*)at;
+    at += 16 * total;
+  }
+  if (values) {
+    o->values = (double*)at;
+    at += 24 * total;
+  }
+  if (touching) o->touching = (uint8_t*)at;
+  return DEM_OK;
+}
+
+// the filled results to the caller's arrays, when the stream has come to them
+int copy_contacts(dem_ctx* c, int64_t total, const ContactsOut& o, int64_t* pairs, double* values,
+                  uint8_t* touching) {
+  if (o.staged) {
+    if (int rc = finish(c)) return rc;
+    if (pairs) memcpy(pairs, o.pairs, 16 * (size_t)total);
+    if (values) memcpy(values, o.values, 24 * (size_t)total);
+    if (touching) memcpy(touching, o.touching, (size_t)total);
+    return DEM_OK;
+  }
+  if (pairs)
+    HIPCHK(hipMemcpyAsync(pairs, o.pairs, 16 * (size_t)total, hipMemcpyDeviceToHost, c->stream));
+  if (values)
+    HIPCHK(hipMemcpyAsync(values, o.values, 24 * (size_t)total, hipMemcpyDeviceToHost, c->stream));
+  if (touching)
+    HIPCHK(hipMemcpyAsync(touching, o.touching, (size_t)total, hipMemcpyDeviceToHost, c->stream));
+  return finish(c);
+}
+
+int read_total(dem_ctx* c, const int* word, int64_t* total) {
+  int v = 0;
+  HIPCHK(hipMemcpyAsync(&v, word, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
+  *total = v;
+  return DEM_OK;
+}
+
+// Candidate pairs of an instance, sorted, with the values that three planes of
+// doubles hold for their entries, into host arrays.
+int contacts_to_host(dem_ctx* c, int32_t instance, int64_t cap, const double* planes,
+                     int64_t* pairs, double* values, uint8_t* touching, int64_t* n_out) {
+  if (c->cap >= ((int64_t)1 << 32))
+    return set_err(DEM_EINVAL, "%lld list entries: too many for 32-bit pair offsets",
+                   (long long)c->cap);
+  const Instance& In = c->inst[(size_t)instance];
+  const int L = c->pcur;
+  int64_t total = 0;
+  const DeviceScope on(c->device);
+  int* scratch = contact_scratch(c);
+  if (In.n > 0) {
+    HIPCHK(launch_contacts_count(c->sp, instance, (int)In.p_begin, In.n, c->info[L], c->gid[L],
+                                 nlist(c, L), scratch, c->stream));
+    if (int rc = read_total(c, contact_starts(scratch, In.n) + In.n, &total)) return rc;
+  }
+  if (n_out) *n_out = total;
+  if (total > cap)
+    return set_err(DEM_EINVAL, "cap %lld < %lld contacts", (long long)cap, (long long)total);
+  if (total == 0) return DEM_OK;
+  ContactsOut o;
+  if (int rc =
+          contacts_out(c, total, pairs != nullptr, values != nullptr, touching != nullptr, &o))
+    return rc;
+  HIPCHK(launch_contacts_fill(c->sp, instance, (int)In.p_begin, c->pos[c->cur], c->info[L],
+                              c->gid[L], nlist(c, L), contact_starts(scratch, In.n), planes,
+                              o.pairs, o.values, o.touching, c->stream));
+  return copy_contacts(c, total, o, pairs, values, touching);
+}
+
 int commit(dem_ctx* c);
 
 // Triangle table and grids of the mesh walls of every instance.  Each mesh
@@ -2030,62 +2136,7 @@ int dem_get_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* pairs, 
   if (int rc = check_instance(c, instance)) return rc;
   if (cap < 0) return set_err(DEM_EINVAL, "cap must be >= 0");
   if (int rc = wait_user(c)) return rc;
-  HostSnapshot h;
-  if (int rc = snapshot(c, h, true)) return rc;
-  const size_t n = (size_t)c->n;
-  std::vector<int> rl(n), nb((size_t)c->cap);
-  std::vector<double> hs((size_t)c->cap * 3);
-  const int L = c->pcur;
-  if (n > 0) {
-    HIPCHK(hipMemcpyAsync(rl.data(), c->rowlen[L], n * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(nb.data(), c->nbr[L], (size_t)c->cap * sizeof(int),
-                          hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(hs.data(), c->hist[L], (size_t)c->cap * 3 * sizeof(double),
-                          hipMemcpyDeviceToHost, c->stream));
-  }
-  if (int rc = finish(c)) return rc;
-  struct Rec {
-    int64_t i, j;
-    double d[3];
-    uint8_t t;
-  };
-  std::vector<Rec> out;
-  const int64_t base = c->inst[(size_t)instance].p_begin;
-  for (size_t p = 0; p < n; ++p) {
-    if ((h.info[p] >> kInstShift) != instance) continue;
-    for (int k = 0; k < rl[p]; ++k) {
-      const int64_t e = nbr_entry((int)p, k, c->max_nb);
-      const int jr = nb[(size_t)e];
-      const int q = jr & 0x7fffffff;  // bit 31: touching at the last evaluation
-      if (h.gid[p] >= h.gid[q]) continue;
-      Rec r;
-      r.i = h.gid[p] - base;
-      r.j = h.gid[q] - base;
-      const bool has_hist = (jr & (int)0x80000000u) != 0;
-      r.d[0] = has_hist ? hs[(size_t)e] : 0.0;
-      r.d[1] = has_hist ? hs[(size_t)c->cap + (size_t)e] : 0.0;
-      r.d[2] = has_hist ? hs[2 * (size_t)c->cap + (size_t)e] : 0.0;
-      const double dx = h.pos[q].x - h.pos[p].x, dy = h.pos[q].y - h.pos[p].y,
-                   dz = h.pos[q].z - h.pos[p].z;
-      const double rsum = h.pos[p].w + h.pos[q].w;
-      r.t = ((dx * dx + dy * dy) + dz * dz) < rsum * rsum ? 1 : 0;
-      out.push_back(r);
-    }
-  }
-  std::sort(out.begin(), out.end(),
-            [](const Rec& a, const Rec& b) { return a.i != b.i ? a.i < b.i : a.j < b.j; });
-  if (n_out) *n_out = (int64_t)out.size();
-  if ((int64_t)out.size() > cap) return set_err(DEM_EINVAL, "cap %lld < %zu contacts", (long long)cap, out.size());
-  for (size_t m = 0; m < out.size(); ++m) {
-    if (pairs) {
-      pairs[2 * m] = out[m].i;
-      pairs[2 * m + 1] = out[m].j;
-    }
-    if (delta_t)
-      for (int k = 0; k < 3; ++k) delta_t[3 * m + k] = out[m].d[k];
-    if (touching) touching[m] = out[m].t;
-  }
-  return DEM_OK;
+  return contacts_to_host(c, instance, cap, c->hist[c->pcur], pairs, delta_t, touching, n_out);
 }
 
 int dem_restore(dem_ctx* c, int32_t instance, int64_t n_pairs, const int64_t* pairs,
@@ -2116,107 +2167,100 @@ int dem_restore(dem_ctx* c, int32_t instance, int64_t n_pairs, const int64_t* pa
       if (int rc = flags_to_error(c, flags)) return rc;
     }
   }
-  HostSnapshot h;
-  if (int rc = snapshot(c, h, true)) return rc;
-  const size_t n = (size_t)c->n;
-  const int L = c->pcur;
   const Instance& In = c->inst[(size_t)instance];
-  const int64_t base = In.p_begin;
-  std::vector<int> where((size_t)In.n, -1);  // instance gid -> sorted index
-  for (size_t p = 0; p < n; ++p)
-    if ((h.info[p] >> kInstShift) == instance) where[(size_t)(h.gid[p] - base)] = (int)p;
-  std::vector<int> rl(n), nb((size_t)c->cap);
-  std::vector<double> hs((size_t)c->cap * 3);
-  std::vector<int> w(n * kWallSlots);
-  std::vector<double> wh(n * kWallSlots * 3);
-  std::vector<double4> F(n), T(n);
-  if (n > 0) {
-    HIPCHK(hipMemcpyAsync(rl.data(), c->rowlen[L], n * sizeof(int), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(nb.data(), c->nbr[L], (size_t)c->cap * sizeof(int),
-                          hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(hs.data(), c->hist[L], (size_t)c->cap * 3 * sizeof(double),
-                          hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(w.data(), c->wid[L], w.size() * sizeof(int), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(wh.data(), c->whist[L], wh.size() * sizeof(double),
-                          hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(F.data(), c->F[L], n * sizeof(double4), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(T.data(), c->T[L], n * sizeof(double4), hipMemcpyDeviceToHost,
-                          c->stream));
-  }
-  if (int rc = finish(c)) return rc;
-  auto sorted = [&](int64_t g) -> int {
-    return g >= 0 && g < In.n ? where[(size_t)g] : -1;
-  };
-  // entries of this instance start without history, as after a search
-  for (size_t p = 0; p < n; ++p) {
-    if ((h.info[p] >> kInstShift) != instance) continue;
-    for (int a = 0; a < 3 * kWallSlots; ++a) wh[(size_t)a * n + p] = 0.0;
-    for (int k = 0; k < rl[p]; ++k) {
-      const size_t e = (size_t)nbr_entry((int)p, k, c->max_nb);
-      nb[e] &= 0x7fffffff;
-      hs[e] = hs[(size_t)c->cap + e] = hs[2 * (size_t)c->cap + e] = 0.0;
+  if (n_pairs > INT32_MAX || n_wall > INT32_MAX)
+    return set_err(DEM_EINVAL, "too many saved contacts");
+  const DeviceScope on(c->device);
+  const int L = c->pcur;
+  hipStream_t s = c->stream;
+  // device copies of the arguments and the entries found for them, freed when
+  // the call ends
+  struct Temp {
+    void* p = nullptr;
+    ~Temp() {
+      if (p) (void)hipFree(p);
+    }
+  } temp;
+  const size_t force_bytes = 24 * (size_t)In.n;
+  size_t bytes = 8 + (size_t)n_pairs * (16 + 24 + 16) + (size_t)n_wall * (16 + 24 + 8) +
+                 (force ? force_bytes : 0) + (torque ? force_bytes : 0);
+  {
+    const hipError_t e = hipMalloc(&temp.p, bytes);
+    if (e != hipSuccess) {
+      temp.p = nullptr;
+      return set_err(DEM_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
     }
   }
-  // a pair that does not touch at the current positions keeps no history:
-  // the first force evaluation, here, would restart it at zero (and the row
-  // cuts of the force kernel may not read its entry until it can touch)
-  auto set_entry = [&](int p, int q, double sgn, const double* d) -> bool {
-    for (int k = 0; k < rl[(size_t)p]; ++k) {
-      const size_t e = (size_t)nbr_entry(p, k, c->max_nb);
-      if ((nb[e] & 0x7fffffff) != q) continue;
-      const double4 xp = h.pos[(size_t)p], xq = h.pos[(size_t)q];
-      const double dx = xq.x - xp.x, dy = xq.y - xp.y, dz = xq.z - xp.z;
-      const double rsum = xp.w + xq.w;
-      if (!(((dx * dx + dy * dy) + dz * dz) < rsum * rsum)) return true;
-      nb[e] = q | (int)0x80000000u;
-      for (int a = 0; a < 3; ++a) hs[(size_t)a * (size_t)c->cap + e] = sgn * d[a];
-      return true;
-    }
-    return false;
+  char* at = (char*)temp.p;
+  auto take = [&](size_t size) {
+    char* p = at;
+    at += size;
+    return p;
   };
-  for (int64_t m = 0; m < n_pairs; ++m) {
-    const int p = sorted(pairs[2 * m]), q = sorted(pairs[2 * m + 1]);
-    if (p < 0 || q < 0 || p == q)
+  auto upload = [&](const void* src, size_t size, const void** dst) -> int {
+    char* p = take(size);
+    *dst = p;
+    if (size > 0) HIPCHK(hipMemcpyAsync(p, src, size, hipMemcpyHostToDevice, s));
+    return DEM_OK;
+  };
+  unsigned long long* bad = (unsigned long long*)take(8);
+  SavedPairs vp{}, vw{};
+  const void *d_force = nullptr, *d_torque = nullptr;
+  int rc = DEM_OK;
+  vp.count = n_pairs;
+  vw.count = n_wall;
+  rc = rc ? rc : upload(pairs, 16 * (size_t)n_pairs, (const void**)&vp.pairs);
+  rc = rc ? rc : upload(delta_t, 24 * (size_t)n_pairs, (const void**)&vp.delta);
+  rc = rc ? rc : upload(wall_pairs, 16 * (size_t)n_wall, (const void**)&vw.pairs);
+  rc = rc ? rc : upload(wall_delta_t, 24 * (size_t)n_wall, (const void**)&vw.delta);
+  if (force) rc = rc ? rc : upload(force, force_bytes, &d_force);
+  if (torque) rc = rc ? rc : upload(torque, force_bytes, &d_torque);
+  vp.entry = (int64_t*)take(16 * (size_t)n_pairs);
+  vw.entry = (int64_t*)take(8 * (size_t)n_wall);
+  if (rc) return rc;
+  // which saved contact an entry (a wall slot) takes its history from, in the
+  // words of the other list, which the next search overwrites
+  vp.owner = c->nbr[L ^ 1];
+  vw.owner = c->wid[L ^ 1];
+  const int* where = c->rank;
+  HIPCHK(launch_place(c->n, instance, (int)In.p_begin, c->info[L], c->gid[L], c->rank, s));
+  // look everything up before anything is changed; the pairs come first
+  for (int walls = 0; walls < 2; ++walls) {
+    const SavedPairs& v = walls ? vw : vp;
+    if (v.count == 0) continue;
+    HIPCHK(launch_fill_i32((int*)bad, 0x7fffffff, 2, s));
+    if (!walls) {
+      HIPCHK(launch_fill_i32(vp.owner, -1, c->cap, s));
+      HIPCHK(launch_restore_find(c->sp, In.n, where, nlist(c, L), vp, bad, s));
+    } else {
+      HIPCHK(launch_fill_i32(vw.owner, -1, (int64_t)c->n * kWallSlots, s));
+      HIPCHK(launch_restore_find_walls(c->n, In.n, In.w_begin, (int)In.walls.size(), where,
+                                       wslots(c, L), vw, bad, s));
+    }
+    unsigned long long first = 0;
+    HIPCHK(hipMemcpyAsync(&first, bad, sizeof(first), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    const int64_t m = (int64_t)(first >> 1);
+    if (m >= v.count) continue;
+    if (!walls && !(first & 1))
       return set_err(DEM_EINVAL, "pair %lld: particle out of range", (long long)m);
-    // history of i -> j, and the exact negative from j's side
-    if (!set_entry(p, q, 1.0, delta_t + 3 * m) || !set_entry(q, p, -1.0, delta_t + 3 * m))
+    if (!walls)
       return set_err(DEM_EINVAL, "pair (%lld, %lld) is not in the contact list",
                      (long long)pairs[2 * m], (long long)pairs[2 * m + 1]);
+    if (!(first & 1)) return set_err(DEM_EINVAL, "wall contact %lld out of range", (long long)m);
+    return set_err(DEM_EINVAL, "particle %lld is not a candidate of wall %lld",
+                   (long long)wall_pairs[2 * m], (long long)wall_pairs[2 * m + 1]);
   }
-  for (int64_t m = 0; m < n_wall; ++m) {
-    const int p = sorted(wall_pairs[2 * m]);
-    const int64_t wall = wall_pairs[2 * m + 1];
-    if (p < 0 || wall < 0 || wall >= (int64_t)In.walls.size())
-      return set_err(DEM_EINVAL, "wall contact %lld out of range", (long long)m);
-    bool found = false;
-    for (int sl = 0; sl < kWallSlots && !found; ++sl) {
-      if (w[(size_t)sl * n + (size_t)p] != In.w_begin + (int)wall) continue;
-      for (int a = 0; a < 3; ++a) wh[(size_t)(3 * sl + a) * n + (size_t)p] = wall_delta_t[3 * m + a];
-      found = true;
-    }
-    if (!found)
-      return set_err(DEM_EINVAL, "particle %lld is not a candidate of wall %lld",
-                     (long long)wall_pairs[2 * m], (long long)wall);
-  }
-  for (int64_t g = 0; g < In.n && (force || torque); ++g) {
-    const size_t p = (size_t)where[(size_t)g];
-    if (force) F[p] = make_double4(force[3 * g], force[3 * g + 1], force[3 * g + 2], 0.0);
-    if (torque) T[p] = make_double4(torque[3 * g], torque[3 * g + 1], torque[3 * g + 2], 0.0);
-  }
-  if (n > 0) {
-    HIPCHK(hipMemcpyAsync(c->nbr[L], nb.data(), (size_t)c->cap * sizeof(int),
-                          hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(c->hist[L], hs.data(), (size_t)c->cap * 3 * sizeof(double),
-                          hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(c->whist[L], wh.data(), wh.size() * sizeof(double),
-                          hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(c->F[L], F.data(), n * sizeof(double4), hipMemcpyHostToDevice,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(c->T[L], T.data(), n * sizeof(double4), hipMemcpyHostToDevice,
-                          c->stream));
+  if (c->n > 0) {
+    // entries of this instance start without history, as after a search
+    HIPCHK(launch_restore_clear(c->sp, instance, c->info[L], nlist(c, L), wslots(c, L), s));
+    if (n_pairs > 0)
+      HIPCHK(launch_restore_apply(c->sp, where, c->pos[c->cur], nlist(c, L), vp, s));
+    if (n_wall > 0) HIPCHK(launch_restore_apply_walls(c->n, wslots(c, L), vw, s));
+    if (force && In.n > 0)
+      HIPCHK(launch_rows_in(In.n, where, (const double*)d_force, c->F[L], s));
+    if (torque && In.n > 0)
+      HIPCHK(launch_rows_in(In.n, where, (const double*)d_torque, c->T[L], s));
   }
   if (step >= 0 && !moving) {
     c->step = step;
@@ -2435,57 +2479,9 @@ int dem_get_contact_forces(dem_ctx* c, int32_t instance, int64_t cap, int64_t* p
                    "the last step ended with a contact search (explicit Euler): the record "
                    "belongs to the previous contact list");
   if (int rc = wait_user(c)) return rc;
-  HostSnapshot h;
-  if (int rc = snapshot(c, h, false)) return rc;
-  const size_t n = (size_t)c->n;
-  std::vector<int> rl(n), nb((size_t)c->cap);
-  std::vector<double> pf((size_t)c->cap * 3);
-  const int L = c->pcur;
-  if (n > 0) {
-    HIPCHK(hipMemcpyAsync(rl.data(), c->rowlen[L], n * sizeof(int), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(nb.data(), c->nbr[L], (size_t)c->cap * sizeof(int),
-                          hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(pf.data(), c->pair_force, (size_t)c->cap * 3 * sizeof(double),
-                          hipMemcpyDeviceToHost, c->stream));
-  }
-  if (int rc = finish(c)) return rc;
-  struct Rec {
-    int64_t i, j;
-    double f[3];
-  };
-  std::vector<Rec> out;
-  const int64_t base = c->inst[(size_t)instance].p_begin;
-  for (size_t p = 0; p < n; ++p) {
-    if ((h.info[p] >> kInstShift) != instance) continue;
-    for (int k = 0; k < rl[p]; ++k) {
-      const int64_t e = nbr_entry((int)p, k, c->max_nb);
-      const int jr = nb[(size_t)e];
-      const int q = jr & 0x7fffffff;
-      if (h.gid[p] >= h.gid[q]) continue;
-      // bit 31: the pair touched at the last evaluation, which wrote its force
-      const bool t = (jr & (int)0x80000000u) != 0;
-      Rec r;
-      r.i = h.gid[p] - base;
-      r.j = h.gid[q] - base;
-      for (int a = 0; a < 3; ++a) r.f[a] = t ? pf[(size_t)a * (size_t)c->cap + (size_t)e] : 0.0;
-      out.push_back(r);
-    }
-  }
-  std::sort(out.begin(), out.end(),
-            [](const Rec& a, const Rec& b) { return a.i != b.i ? a.i < b.i : a.j < b.j; });
-  if (n_out) *n_out = (int64_t)out.size();
-  if ((int64_t)out.size() > cap)
-    return set_err(DEM_EINVAL, "cap %lld < %zu pairs", (long long)cap, out.size());
-  for (size_t m = 0; m < out.size(); ++m) {
-    if (pairs) {
-      pairs[2 * m] = out[m].i;
-      pairs[2 * m + 1] = out[m].j;
-    }
-    if (force)
-      for (int a = 0; a < 3; ++a) force[3 * m + a] = out[m].f[a];
-  }
-  return DEM_OK;
+  // the top bit of an entry: the pair touched at the last evaluation, which
+  // wrote its force
+  return contacts_to_host(c, instance, cap, c->pair_force, pairs, force, nullptr, n_out);
 }
 
 int dem_get_wall_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* pairs,
@@ -2494,49 +2490,26 @@ int dem_get_wall_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* pa
   if (int rc = check_instance(c, instance)) return rc;
   if (cap < 0) return set_err(DEM_EINVAL, "cap must be >= 0");
   if (int rc = wait_user(c)) return rc;
-  HostSnapshot h;
-  if (int rc = snapshot(c, h, false)) return rc;
-  const size_t n = (size_t)c->n;
-  std::vector<int> w(n * kWallSlots);
-  std::vector<double> wh(n * kWallSlots * 3);
-  if (n > 0) {
-    HIPCHK(hipMemcpyAsync(w.data(), c->wid[c->pcur], w.size() * sizeof(int), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(wh.data(), c->whist[c->pcur], wh.size() * sizeof(double),
-                          hipMemcpyDeviceToHost, c->stream));
-  }
-  if (int rc = finish(c)) return rc;
-  struct Rec {
-    int64_t i, w;
-    double d[3];
-  };
-  std::vector<Rec> out;
   const Instance& In = c->inst[(size_t)instance];
-  for (size_t p = 0; p < n; ++p) {
-    if ((h.info[p] >> kInstShift) != instance) continue;
-    for (int s = 0; s < kWallSlots; ++s) {
-      const int wi = w[(size_t)s * n + p];
-      if (wi < 0) break;
-      Rec r;
-      r.i = h.gid[p] - In.p_begin;
-      r.w = wi - In.w_begin;
-      for (int k = 0; k < 3; ++k) r.d[k] = wh[(size_t)(3 * s + k) * n + p];
-      out.push_back(r);
-    }
+  int64_t total = 0;
+  const DeviceScope on(c->device);
+  const int L = c->pcur;
+  int* scratch = contact_scratch(c);
+  if (In.n > 0) {
+    HIPCHK(launch_wall_contacts_count(c->n, instance, (int)In.p_begin, In.n, c->info[L],
+                                      c->gid[L], wslots(c, L), scratch, c->stream));
+    if (int rc = read_total(c, contact_starts(scratch, In.n) + In.n, &total)) return rc;
   }
-  std::sort(out.begin(), out.end(),
-            [](const Rec& a, const Rec& b) { return a.i != b.i ? a.i < b.i : a.w < b.w; });
-  if (n_out) *n_out = (int64_t)out.size();
-  if ((int64_t)out.size() > cap) return set_err(DEM_EINVAL, "cap %lld < %zu wall contacts", (long long)cap, out.size());
-  for (size_t m = 0; m < out.size(); ++m) {
-    if (pairs) {
-      pairs[2 * m] = out[m].i;
-      pairs[2 * m + 1] = out[m].w;
-    }
-    if (delta_t)
-      for (int k = 0; k < 3; ++k) delta_t[3 * m + k] = out[m].d[k];
-  }
-  return DEM_OK;
+  if (n_out) *n_out = total;
+  if (total > cap)
+    return set_err(DEM_EINVAL, "cap %lld < %lld wall contacts", (long long)cap, (long long)total);
+  if (total == 0) return DEM_OK;
+  ContactsOut o;
+  if (int rc = contacts_out(c, total, pairs != nullptr, delta_t != nullptr, false, &o)) return rc;
+  HIPCHK(launch_wall_contacts_fill(c->n, instance, (int)In.p_begin, In.w_begin, c->info[L],
+                                   c->gid[L], wslots(c, L), contact_starts(scratch, In.n), o.pairs,
+                                   o.values, c->stream));
+  return copy_contacts(c, total, o, pairs, delta_t, nullptr);
 }
 
 int dem_resort(dem_ctx* c) {

@@ -314,6 +314,59 @@ hipError_t launch_place(int n_all, int inst, int gid_base, const int* info, cons
 hipError_t launch_rows_out(int64_t n, const int* at, const RowsOut& r, const int* info,
                            hipStream_t s);
 
+// Contact lists of an instance (n particles, gids from gid_base) in input order.
+// scratch: contact_scratch_ints(n) ints.  *_count leaves the pairs' (a wall
+// candidate's) first place per gid in contact_starts(scratch, n)[0 .. n], the
+// total last; *_fill writes them there, each gid's sorted.  planes: three
+// planes of l.cap doubles, whose values an entry with its top bit set stands
+// for (else zeros).  Any output may be null.
+int64_t contact_scratch_ints(int64_t n);
+int* contact_starts(int* scratch, int64_t n);
+hipError_t launch_contacts_count(const StepParams& sp, int inst, int gid_base, int64_t n,
+                                 const int* info, const int* gid, NbrList l, int* scratch,
+                                 hipStream_t s);
+hipError_t launch_contacts_fill(const StepParams& sp, int inst, int gid_base, const double4* pos,
+                                const int* info, const int* gid, NbrList l, const int* starts,
+                                const double* planes, int64_t* pairs, double* values,
+                                uint8_t* touching, hipStream_t s);
+hipError_t launch_wall_contacts_count(int n_all, int inst, int gid_base, int64_t n,
+                                      const int* info, const int* gid, WallSlots ws, int* scratch,
+                                      hipStream_t s);
+hipError_t launch_wall_contacts_fill(int n_all, int inst, int gid_base, int w_begin,
+                                     const int* info, const int* gid, WallSlots ws,
+                                     const int* starts, int64_t* pairs, double* delta_t,
+                                     hipStream_t s);
+
+// Histories of saved contacts back into the lists (dem_restore).  at: sorted
+// index per gid (launch_place); n: particles of the instance.  The find
+// kernels look every contact's entries up (entry: two per pair, slot: one per
+// wall contact), note the last contact that names an entry in owner (preset to
+// -1) and lower *bad (preset to INT64_MAX) to 2 m (out of range) or 2 m + 1
+// (not in the lists) for the first contact m that fails; the apply kernels
+// write the histories of the owners.
+struct SavedPairs {
+  int64_t count;
+  const int64_t* pairs;
+  const double* delta;
+  int64_t* entry;
+  int* owner;
+};
+hipError_t launch_restore_find(const StepParams& sp, int64_t n, const int* at, NbrList l,
+                               const SavedPairs& v, unsigned long long* bad, hipStream_t s);
+hipError_t launch_restore_apply(const StepParams& sp, const int* at, const double4* pos,
+                                NbrList l, const SavedPairs& v, hipStream_t s);
+hipError_t launch_restore_find_walls(int n_all, int64_t n, int w_begin, int n_walls,
+                                     const int* at, WallSlots ws, const SavedPairs& v,
+                                     unsigned long long* bad, hipStream_t s);
+hipError_t launch_restore_apply_walls(int n_all, WallSlots ws, const SavedPairs& v,
+                                      hipStream_t s);
+// every entry and wall slot of an instance without history
+hipError_t launch_restore_clear(const StepParams& sp, int inst, const int* info, NbrList l,
+                                WallSlots ws, hipStream_t s);
+// dst[at[g]] = (src[3 g ..], 0), g < n
+hipError_t launch_rows_in(int64_t n, const int* at, const double* src, double4* dst,
+                          hipStream_t s);
+
 // Candidate pairs of instance inst on the device (see dem_get_contacts_device).
 // scratch holds pairs_scratch_ints(sp.n) ints: block counts, their exclusive
 // scan (scratch[nb + nb] is the total afterwards) and the scan's tile sums.

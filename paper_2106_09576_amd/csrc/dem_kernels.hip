@@ -23,6 +23,8 @@
 // particle (ping-pong state buffers), so a time step is one launch.
 #include "dem_device.hpp"
 
+#include <algorithm>
+
 namespace demgpu {
 
 // ------------------------------------------------------------------ helpers
@@ -2301,6 +2303,275 @@ hipError_t launch_pairs_fill(const StepParams& sp, int inst, int gid_base, const
   if (nb == 0) return hipSuccess;
   hipLaunchKernelGGL(k_pairs_fill, dim3((unsigned)nb), dim3(kBlock), 0, s, sp, inst, gid_base,
                      pos, info, gid, l, scratch + nb, pairs, delta_t, touching);
+  return hipGetLastError();
+}
+
+// -------------------------------------------------- contacts in input order
+//
+// One thread per particle: a count per gid, a scan, and a fill in which each
+// thread writes its pairs in the order of the other gid (a row is short enough
+// to rank every entry against the whole row).  The lists used to be copied to
+// the host whole (28 bytes for every one of max_nb entries per particle) and
+// filtered and sorted there: 35 ms and more for 100,000 spheres; now bound by
+// the copy of the results.
+
+int64_t contact_scratch_ints(int64_t n) {
+  return n + (n + 2) + ((n + kScanTile - 1) / kScanTile + 1);
+}
+int* contact_starts(int* scratch, int64_t n) { return scratch + n; }
+
+__global__ void k_contacts_count(StepParams sp, int inst, int gid_base,
+                                 const int* __restrict__ info, const int* __restrict__ gid,
+                                 NbrList l, int* __restrict__ count) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (p >= sp.n || (info[p] >> kInstShift) != inst) return;
+  count[gid[p] - gid_base] = pairs_of_row(sp, inst, p, info, gid, l);
+}
+
+__global__ void k_contacts_fill(StepParams sp, int inst, int gid_base,
+                                const double4* __restrict__ pos, const int* __restrict__ info,
+                                const int* __restrict__ gid, NbrList l,
+                                const int* __restrict__ starts, const double* __restrict__ planes,
+                                int64_t* __restrict__ pairs, double* __restrict__ values,
+                                uint8_t* __restrict__ touching) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (p >= sp.n || (info[p] >> kInstShift) != inst || (info[p] & kInactive)) return;
+  const int g = gid[p];
+  const int64_t first = starts[g - gid_base];
+  if (starts[g - gid_base + 1] == first) return;
+  const double4 xp = pos[p];
+  const int len = l.rowlen[p];
+  for (int k = 0; k < len; ++k) {
+    const int64_t e = nbr_entry(p, k, sp.max_nb);
+    const int jr = l.nbr[e];
+    const int q = jr & kIndexMask;
+    const int gq = gid[q];
+    if (!(gq > g)) continue;
+    int64_t o = first;
+    for (int m = 0; m < len; ++m) {
+      const int gm = gid[l.nbr[nbr_entry(p, m, sp.max_nb)] & kIndexMask];
+      o += gm > g && gm < gq ? 1 : 0;
+    }
+    if (pairs) {
+      pairs[2 * o] = g - gid_base;
+      pairs[2 * o + 1] = gq - gid_base;
+    }
+    if (values) {
+      const bool h = (jr & kTouchedBit) != 0;
+      for (int a = 0; a < 3; ++a) values[3 * o + a] = h ? planes[a * l.cap + e] : 0.0;
+    }
+    if (touching) {
+      const double4 xq = pos[q];
+      const double dx = xq.x - xp.x, dy = xq.y - xp.y, dz = xq.z - xp.z;
+      const double d2 = (dx * dx + dy * dy) + dz * dz;
+      const double rs = xp.w + xq.w;
+      touching[o] = d2 < rs * rs ? 1 : 0;
+    }
+  }
+}
+
+__global__ void k_wall_contacts_count(int n_all, int inst, int gid_base,
+                                      const int* __restrict__ info, const int* __restrict__ gid,
+                                      WallSlots ws, int* __restrict__ count) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (p >= n_all || (info[p] >> kInstShift) != inst) return;
+  int c = 0;
+  while (c < kWallSlots && ws.wid[(int64_t)c * n_all + p] >= 0) ++c;
+  count[gid[p] - gid_base] = c;
+}
+
+// a particle's slots are in the order of the walls
+__global__ void k_wall_contacts_fill(int n_all, int inst, int gid_base, int w_begin,
+                                     const int* __restrict__ info, const int* __restrict__ gid,
+                                     WallSlots ws, const int* __restrict__ starts,
+                                     int64_t* __restrict__ pairs, double* __restrict__ delta_t) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (p >= n_all || (info[p] >> kInstShift) != inst) return;
+  const int g = gid[p] - gid_base;
+  const int64_t o = starts[g];
+  const int c = starts[g + 1] - (int)o;
+  for (int s = 0; s < c; ++s) {
+    if (pairs) {
+      pairs[2 * (o + s)] = g;
+      pairs[2 * (o + s) + 1] = ws.wid[(int64_t)s * n_all + p] - w_begin;
+    }
+    if (delta_t)
+      for (int a = 0; a < 3; ++a)
+        delta_t[3 * (o + s) + a] = ws.hist[(int64_t)(3 * s + a) * n_all + p];
+  }
+}
+
+static inline dim3 one_per_thread(int64_t n) {
+  return dim3((unsigned)std::max<int64_t>((n + kBlock - 1) / kBlock, 1));
+}
+
+static hipError_t scan_counts(int64_t n, int* scratch, hipStream_t s) {
+  return launch_scan(scratch, scratch + n, n, scratch + n + (n + 2), s);
+}
+
+hipError_t launch_contacts_count(const StepParams& sp, int inst, int gid_base, int64_t n,
+                                 const int* info, const int* gid, NbrList l, int* scratch,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL(k_contacts_count, one_per_thread(sp.n), dim3(kBlock), 0, s, sp, inst,
+                     gid_base, info, gid, l, scratch);
+  return scan_counts(n, scratch, s);
+}
+
+hipError_t launch_contacts_fill(const StepParams& sp, int inst, int gid_base, const double4* pos,
+                                const int* info, const int* gid, NbrList l, const int* starts,
+                                const double* planes, int64_t* pairs, double* values,
+                                uint8_t* touching, hipStream_t s) {
+  hipLaunchKernelGGL(k_contacts_fill, one_per_thread(sp.n), dim3(kBlock), 0, s, sp, inst, gid_base,
+                     pos, info, gid, l, starts, planes, pairs, values, touching);
+  return hipGetLastError();
+}
+
+hipError_t launch_wall_contacts_count(int n_all, int inst, int gid_base, int64_t n,
+                                      const int* info, const int* gid, WallSlots ws, int* scratch,
+                                      hipStream_t s) {
+  hipLaunchKernelGGL(k_wall_contacts_count, one_per_thread(n_all), dim3(kBlock), 0, s, n_all, inst,
+                     gid_base, info, gid, ws, scratch);
+  return scan_counts(n, scratch, s);
+}
+
+hipError_t launch_wall_contacts_fill(int n_all, int inst, int gid_base, int w_begin,
+                                     const int* info, const int* gid, WallSlots ws,
+                                     const int* starts, int64_t* pairs, double* delta_t,
+                                     hipStream_t s) {
+  hipLaunchKernelGGL(k_wall_contacts_fill, one_per_thread(n_all), dim3(kBlock), 0, s, n_all, inst,
+                     gid_base, w_begin, info, gid, ws, starts, pairs, delta_t);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------ exact resume
+
+__global__ void k_restore_find(StepParams sp, int64_t n, const int* __restrict__ at, NbrList l,
+                               SavedPairs v, unsigned long long* __restrict__ bad) {
+  const int64_t m = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (m >= v.count) return;
+  const int64_t gi = v.pairs[2 * m], gj = v.pairs[2 * m + 1];
+  if (gi < 0 || gi >= n || gj < 0 || gj >= n || gi == gj) {
+    atomicMin(bad, 2ull * (unsigned long long)m);
+    return;
+  }
+  const int pq[2] = {at[gi], at[gj]};
+  for (int side = 0; side < 2; ++side) {
+    const int p = pq[side], q = pq[1 - side];
+    int64_t e = -1;
+    const int len = l.rowlen[p];
+    for (int k = 0; k < len && e < 0; ++k) {
+      const int64_t t = nbr_entry(p, k, sp.max_nb);
+      if ((l.nbr[t] & kIndexMask) == q) e = t;
+    }
+    v.entry[2 * m + side] = e;
+    if (e < 0)
+      atomicMin(bad, 2ull * (unsigned long long)m + 1ull);
+    else
+      atomicMax(v.owner + e, (int)m);
+  }
+}
+
+// A pair that does not touch at the current positions keeps no history: the
+// first force evaluation, here, would restart it at zero (and the row cuts of
+// the force kernel may not read its entry until it can touch).
+__global__ void k_restore_apply(StepParams sp, const int* __restrict__ at,
+                                const double4* __restrict__ pos, NbrList l, SavedPairs v) {
+  const int64_t m = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (m >= v.count) return;
+  const double4 xp = pos[at[v.pairs[2 * m]]], xq = pos[at[v.pairs[2 * m + 1]]];
+  const double dx = xq.x - xp.x, dy = xq.y - xp.y, dz = xq.z - xp.z;
+  const double rsum = xp.w + xq.w;
+  if (!(((dx * dx + dy * dy) + dz * dz) < rsum * rsum)) return;
+  for (int side = 0; side < 2; ++side) {
+    const int64_t e = v.entry[2 * m + side];
+    if (v.owner[e] != (int)m) continue;
+    // history of i -> j, and the exact negative from j's side
+    const double sgn = side == 0 ? 1.0 : -1.0;
+    l.nbr[e] |= kTouchedBit;
+    for (int a = 0; a < 3; ++a) l.hist[a * l.cap + e] = sgn * v.delta[3 * m + a];
+  }
+}
+
+__global__ void k_restore_find_walls(int n_all, int64_t n, int w_begin, int n_walls,
+                                     const int* __restrict__ at, WallSlots ws, SavedPairs v,
+                                     unsigned long long* __restrict__ bad) {
+  const int64_t m = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (m >= v.count) return;
+  const int64_t g = v.pairs[2 * m], w = v.pairs[2 * m + 1];
+  if (g < 0 || g >= n || w < 0 || w >= n_walls) {
+    atomicMin(bad, 2ull * (unsigned long long)m);
+    return;
+  }
+  int64_t slot = -1;
+  for (int s = 0; s < kWallSlots && slot < 0; ++s)
+    if (ws.wid[(int64_t)s * n_all + at[g]] == w_begin + (int)w) slot = (int64_t)s * n_all + at[g];
+  v.entry[m] = slot;
+  if (slot < 0)
+    atomicMin(bad, 2ull * (unsigned long long)m + 1ull);
+  else
+    atomicMax(v.owner + slot, (int)m);
+}
+
+__global__ void k_restore_apply_walls(int n_all, WallSlots ws, SavedPairs v) {
+  const int64_t m = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (m >= v.count || v.owner[v.entry[m]] != (int)m) return;
+  const int64_t s = v.entry[m] / n_all, p = v.entry[m] - s * n_all;
+  for (int a = 0; a < 3; ++a) ws.hist[(3 * s + a) * n_all + p] = v.delta[3 * m + a];
+}
+
+__global__ void k_restore_clear(StepParams sp, int inst, const int* __restrict__ info, NbrList l,
+                                WallSlots ws) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (p >= sp.n || (info[p] >> kInstShift) != inst) return;
+  for (int a = 0; a < 3 * kWallSlots; ++a) ws.hist[(int64_t)a * sp.n + p] = 0.0;
+  const int len = l.rowlen[p];
+  for (int k = 0; k < len; ++k) {
+    const int64_t e = nbr_entry(p, k, sp.max_nb);
+    const int jr = l.nbr[e];
+    if (jr & kTouchedBit) l.nbr[e] = jr & kIndexMask;
+  }
+}
+
+__global__ void k_rows_in(int64_t n, const int* __restrict__ at, const double* __restrict__ src,
+                          double4* __restrict__ dst) {
+  const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (g < n) dst[at[g]] = make_double4(src[3 * g], src[3 * g + 1], src[3 * g + 2], 0.0);
+}
+
+hipError_t launch_restore_find(const StepParams& sp, int64_t n, const int* at, NbrList l,
+                               const SavedPairs& v, unsigned long long* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_restore_find, one_per_thread(v.count), dim3(kBlock), 0, s, sp, n, at, l, v,
+                     bad);
+  return hipGetLastError();
+}
+hipError_t launch_restore_apply(const StepParams& sp, const int* at, const double4* pos,
+                                NbrList l, const SavedPairs& v, hipStream_t s) {
+  hipLaunchKernelGGL(k_restore_apply, one_per_thread(v.count), dim3(kBlock), 0, s, sp, at, pos, l,
+                     v);
+  return hipGetLastError();
+}
+hipError_t launch_restore_find_walls(int n_all, int64_t n, int w_begin, int n_walls,
+                                     const int* at, WallSlots ws, const SavedPairs& v,
+                                     unsigned long long* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_restore_find_walls, one_per_thread(v.count), dim3(kBlock), 0, s, n_all, n,
+                     w_begin, n_walls, at, ws, v, bad);
+  return hipGetLastError();
+}
+hipError_t launch_restore_apply_walls(int n_all, WallSlots ws, const SavedPairs& v,
+                                      hipStream_t s) {
+  hipLaunchKernelGGL(k_restore_apply_walls, one_per_thread(v.count), dim3(kBlock), 0, s, n_all, ws,
+                     v);
+  return hipGetLastError();
+}
+hipError_t launch_restore_clear(const StepParams& sp, int inst, const int* info, NbrList l,
+                                WallSlots ws, hipStream_t s) {
+  hipLaunchKernelGGL(k_restore_clear, one_per_thread(sp.n), dim3(kBlock), 0, s, sp, inst, info, l,
+                     ws);
+  return hipGetLastError();
+}
+hipError_t launch_rows_in(int64_t n, const int* at, const double* src, double4* dst,
+                          hipStream_t s) {
+  hipLaunchKernelGGL(k_rows_in, one_per_thread(n), dim3(kBlock), 0, s, n, at, src, dst);
   return hipGetLastError();
 }
 
