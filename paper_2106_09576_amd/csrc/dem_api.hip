@@ -346,14 +346,20 @@ int enqueue_rebuild(dem_ctx* c, int check_guard, int move_forces, int64_t step_r
   if (bound_step_rel < 0) bound_step_rel = step_rel;
   hipStream_t s = c->stream;
   const int a = c->cur, p = c->pcur;
-  HIPCHK(launch_fill_i32(c->count, 0, c->n_keys + 1, s));
-  HIPCHK(launch_keys(c->d_inst, c->sp, c->pos[a], c->vel[a], c->info[p], c->xref, check_guard,
-                     c->keys, c->rank, c->count, c->d_flags, s));
-  HIPCHK(launch_scan(c->count, c->start, c->n_keys + 1, c->tile_sums, s, c->d_key_cell, c->d_cse,
-                     c->n_keys));
-  HIPCHK(launch_scatter(c->n, c->keys, c->rank, c->start, c->perm0, s));
-  HIPCHK(launch_cell_rank(c->n, c->n_keys, c->perm0, c->keys, c->start, c->gid[p],
-                          c->perm, s));
+  if (small_sort_fits(c->n, c->n_keys)) {
+    HIPCHK(launch_sort_small(c->d_inst, c->sp, c->pos[a], c->vel[a], c->info[p], c->xref,
+                             check_guard, c->gid[p], c->d_key_cell, c->d_cse, c->start, c->perm,
+                             c->d_flags, s));
+  } else {
+    HIPCHK(launch_fill_i32(c->count, 0, c->n_keys + 1, s));
+    HIPCHK(launch_keys(c->d_inst, c->sp, c->pos[a], c->vel[a], c->info[p], c->xref, check_guard,
+                       c->keys, c->rank, c->count, c->d_flags, s));
+    HIPCHK(launch_scan(c->count, c->start, c->n_keys + 1, c->tile_sums, s, c->d_key_cell, c->d_cse,
+                       c->n_keys));
+    HIPCHK(launch_scatter(c->n, c->keys, c->rank, c->start, c->perm0, s));
+    HIPCHK(launch_cell_rank(c->n, c->n_keys, c->perm0, c->keys, c->start, c->gid[p],
+                            c->perm, s));
+  }
   HIPCHK(launch_reorder(c->sp, c->d_inst, c->perm, c->inv, pbufs(c, a), pbufs(c, a ^ 1),
                         c->gid[p],
                         c->gid[p ^ 1],

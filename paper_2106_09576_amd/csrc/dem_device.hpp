@@ -239,6 +239,13 @@ hipError_t launch_scatter(int n, const uint32_t* keys, const int* rank, const in
                           int* perm0, hipStream_t s);
 hipError_t launch_cell_rank(int n, int64_t n_keys, const int* perm0, const uint32_t* keys,
                             const int* start, const int* gid, int* perm, hipStream_t s);
+// The whole sort (launch_fill_i32 .. launch_cell_rank) in one workgroup, for
+// contexts that small_sort_fits: start, cse and perm as those leave them.
+bool small_sort_fits(int n, int64_t n_keys);
+hipError_t launch_sort_small(const InstDev* inst, const StepParams& sp, const double4* pos,
+                             const double4* vel, int* info, const double4* xref, int check_guard,
+                             const int* gid, const uint32_t* key_cell, int2* cse, int* start,
+                             int* perm, int* flags, hipStream_t s);
 // perm: new -> old index; inv receives old -> new
 // The particle-wall and particle-triangle searches take the walls where they
 // are at time (*clock + step_rel) dt.

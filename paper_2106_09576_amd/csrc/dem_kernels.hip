@@ -84,9 +84,42 @@ hipError_t launch_fill_i32(int* p, int v, int64_t n, hipStream_t s) {
 
 // ------------------------------------------------------------- sort: keys
 
-// Cell key of every particle; deactivates particles outside the domain box,
-// checks the displacement guard and non-finite states, counts per cell (the
-// returned atomic slot is the particle's provisional rank in its cell).
+// Cell key of particle i; deactivates it outside the domain box, checks the
+// displacement guard and the state.
+__device__ __forceinline__ uint32_t particle_key(const InstDev* __restrict__ inst,
+                                                 const StepParams& sp, int i,
+                                                 const double4* __restrict__ pos,
+                                                 const double4* __restrict__ vel,
+                                                 int* __restrict__ info,
+                                                 const double4* __restrict__ xref,
+                                                 int check_guard, int* __restrict__ flags) {
+  const int inf = info[i];
+  if (inf & kInactive) return sp.n_keys;
+  const InstDev& I = inst[inf >> kInstShift];
+  const GridDev& g = I.grid;
+  const double4 p = pos[i];
+  const double4 v = vel[i];
+  if (!finite3(p.x, p.y, p.z) || !finite3(v.x, v.y, v.z)) atomicOr(flags, kFlagNonFinite);
+  if (check_guard) {
+    const double4 r = xref[i];
+    const double dx = p.x - r.x, dy = p.y - r.y, dz = p.z - r.z;
+    const double d2 = (dx * dx + dy * dy) + dz * dz;
+    if (d2 > I.guard2) atomicOr(flags, kFlagGuard);
+  }
+  const bool inside = p.x >= g.lo[0] && p.x < g.hi[0] && p.y >= g.lo[1] && p.y < g.hi[1] &&
+                      p.z >= g.lo[2] && p.z < g.hi[2];
+  if (!inside) {
+    info[i] = inf | kInactive;
+    return sp.n_keys;
+  }
+  const int cx = cell_coord(p.x, g.lo[0], g.h, g.nc[0]);
+  const int cy = cell_coord(p.y, g.lo[1], g.h, g.nc[1]);
+  const int cz = cell_coord(p.z, g.lo[2], g.h, g.nc[2]);
+  return I.key_base + cell_key(g, cx, cy, cz);
+}
+
+// Cell key of every particle, counted per cell (the returned atomic slot is
+// the particle's provisional rank in its cell).
 __global__ void k_keys(const InstDev* __restrict__ inst, StepParams sp,
                        const double4* __restrict__ pos,
                        const double4* __restrict__ vel, int* __restrict__ info,
@@ -97,31 +130,8 @@ __global__ void k_keys(const InstDev* __restrict__ inst, StepParams sp,
   // every lane stays to the end: the ranks are handed out per run of equal
   // keys in the wavefront (below)
   const bool valid = i < sp.n;
-  int inf = valid ? info[i] : kInactive;
-  uint32_t key = valid ? sp.n_keys : 0xffffffffu;
-  if (valid && !(inf & kInactive)) {
-    const InstDev& I = inst[inf >> kInstShift];
-    const GridDev& g = I.grid;
-    double4 p = pos[i];
-    double4 v = vel[i];
-    if (!finite3(p.x, p.y, p.z) || !finite3(v.x, v.y, v.z)) atomicOr(flags, kFlagNonFinite);
-    if (check_guard) {
-      double4 r = xref[i];
-      double dx = p.x - r.x, dy = p.y - r.y, dz = p.z - r.z;
-      double d2 = (dx * dx + dy * dy) + dz * dz;
-      if (d2 > I.guard2) atomicOr(flags, kFlagGuard);
-    }
-    bool inside = p.x >= g.lo[0] && p.x < g.hi[0] && p.y >= g.lo[1] && p.y < g.hi[1] &&
-                  p.z >= g.lo[2] && p.z < g.hi[2];
-    if (!inside) {
-      info[i] = inf | kInactive;
-    } else {
-      int cx = cell_coord(p.x, g.lo[0], g.h, g.nc[0]);
-      int cy = cell_coord(p.y, g.lo[1], g.h, g.nc[1]);
-      int cz = cell_coord(p.z, g.lo[2], g.h, g.nc[2]);
-      key = I.key_base + cell_key(g, cx, cy, cz);
-    }
-  }
+  const uint32_t key = valid ? particle_key(inst, sp, i, pos, vel, info, xref, check_guard, flags)
+                             : 0xffffffffu;
   // Particles come in the previous search's spatial order, so lanes with the
   // same cell mostly sit side by side: the first lane of each run of equal
   // keys reserves the whole run with one atomic and hands consecutive ranks
@@ -291,6 +301,116 @@ hipError_t launch_cell_rank(int n, int64_t n_keys, const int* perm0, const uint3
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_cell_rank, dim3(grid_for(n)), dim3(kBlock), 0, s, n, (uint32_t)n_keys,
                      perm0, keys, start, gid, perm);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------- sort: small contexts
+//
+// Keys, counts, their scan, the cells' ranges and the order of the particles by
+// one workgroup, the counts in LDS.  The seven launches it stands for take 20
+// us and the gaps between them for 1,000 particles, all of it latency
+// (search chain 64 -> 52 us).
+
+constexpr int kSortThreads = 1024;
+constexpr int kSortPer = 4;  // particles per thread
+constexpr size_t kSortLds = 64 * 1024 - 256;
+
+// counts (and a total), three words per particle; a scan goes through an odd
+// number of counts per thread, so that the chunks lie on different banks
+static int sort_chunk(int64_t n_keys) {
+  return (int)((n_keys + 1 + kSortThreads - 1) / kSortThreads) | 1;
+}
+static size_t sort_lds(int n, int64_t n_keys) {
+  return sizeof(int) * ((size_t)n_keys + 2 + 3 * (size_t)n);
+}
+bool small_sort_fits(int n, int64_t n_keys) {
+  return n <= kSortThreads * kSortPer && n_keys < 16384 && sort_lds(n, n_keys) <= kSortLds;
+}
+
+__global__ void __launch_bounds__(kSortThreads)
+k_sort_small(const InstDev* __restrict__ inst, StepParams sp, int chunk,
+             const double4* __restrict__ pos, const double4* __restrict__ vel,
+             int* __restrict__ info, const double4* __restrict__ xref, int check_guard,
+             const int* __restrict__ gid, const uint32_t* __restrict__ key_cell,
+             int2* __restrict__ cse, int* __restrict__ start, int* __restrict__ perm,
+             int* __restrict__ flags) {
+  extern __shared__ int sort_lds_words[];
+  __shared__ int sums[kSortThreads / 64];
+  int* at = sort_lds_words;  // counts, then first places; at[m] for the end of key m - 1
+  const int m = (int)sp.n_keys + 1;
+  int* slot_of = at + m + 1;    // particle at each place of its cell, as it arrived
+  int* slot_gid = slot_of + sp.n;
+  int* slot_key = slot_gid + sp.n;
+  const int tid = threadIdx.x;
+  for (int k = tid; k <= m; k += kSortThreads) at[k] = 0;
+  __syncthreads();
+  int key[kSortPer], rank[kSortPer], g[kSortPer];
+#pragma unroll
+  for (int u = 0; u < kSortPer; ++u) {
+    const int i = tid + u * kSortThreads;
+    if (i >= sp.n) continue;
+    g[u] = gid[i];
+    key[u] = (int)particle_key(inst, sp, i, pos, vel, info, xref, check_guard, flags);
+    rank[u] = atomicAdd(&at[key[u]], 1);
+  }
+  __syncthreads();
+  // exclusive scan: a chunk per thread, the chunks' sums over the wavefronts
+  int sum = 0;
+  const int k0 = tid * chunk, k1 = k0 + chunk < m ? k0 + chunk : m;
+  for (int k = k0; k < k1; ++k) sum += at[k];
+  int x = sum;
+  const int lane = tid & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) sums[tid >> 6] = x;
+  __syncthreads();
+  int ex = x - sum;
+  for (int w = 0; w < (tid >> 6); ++w) ex += sums[w];
+  for (int k = k0; k < k1; ++k) {
+    const int v = at[k];
+    at[k] = ex;
+    ex += v;
+  }
+  if (tid == kSortThreads - 1) at[m] = ex;
+  __syncthreads();
+  const int n_keys = (int)sp.n_keys;
+  for (int k = tid; k <= m; k += kSortThreads) {
+    start[k] = at[k];
+    if (k < n_keys) cse[key_cell[k]] = make_int2(at[k], at[k + 1]);
+  }
+#pragma unroll
+  for (int u = 0; u < kSortPer; ++u) {
+    const int i = tid + u * kSortThreads;
+    if (i >= sp.n) continue;
+    const int s = at[key[u]] + rank[u];
+    slot_of[s] = i;
+    slot_gid[s] = g[u];
+    slot_key[s] = key[u];
+  }
+  __syncthreads();
+  // within a cell by gid; inactive particles as they arrived (k_cell_rank)
+  for (int s = tid; s < sp.n; s += kSortThreads) {
+    const int c = slot_key[s];
+    int to = s;
+    if (c != n_keys) {
+      const int own = slot_gid[s];
+      to = at[c];
+      for (int q = at[c]; q < at[c + 1]; ++q) to += slot_gid[q] < own ? 1 : 0;
+    }
+    perm[to] = slot_of[s];
+  }
+}
+
+hipError_t launch_sort_small(const InstDev* inst, const StepParams& sp, const double4* pos,
+                             const double4* vel, int* info, const double4* xref, int check_guard,
+                             const int* gid, const uint32_t* key_cell, int2* cse, int* start,
+                             int* perm, int* flags, hipStream_t s) {
+  hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(kSortThreads), sort_lds(sp.n, sp.n_keys), s, inst,
+                     sp, sort_chunk(sp.n_keys), pos, vel, info, xref, check_guard, gid, key_cell,
+                     cse, start, perm, flags);
   return hipGetLastError();
 }
 

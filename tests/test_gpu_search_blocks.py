@@ -102,3 +102,41 @@ def test_thin_grids(Dem, cells):
         assert np.array_equal(v, b.get_state(1)[k]), k
     a.close()
     b.close()
+
+
+# contexts that one workgroup sorts and the sizes just beyond (4,096 particles,
+# 16,383 cells, 64 KB of LDS): the same order, so the same bits
+@pytest.mark.parametrize("n,extra_cells", [(1, 0), (63, 0), (1023, 0), (1025, 0), (4096, 0),
+                                           (4097, 0), (500, 4000), (500, 14000), (500, 40000)])
+def test_small_sorts(Dem, n, extra_cells):
+    sc = W.dense_snapshot(n=n, seed=n + 1, polydisperse=0.1, K=3, walls=n > 8)
+    # a longer box of empty cells, and a particle that has left it
+    c = sc["config"]
+    h = 1.3 * 2 * float(sc["particles"]["radius"].max())
+    lo, hi = np.array(c["domain_lo"]), np.array(c["domain_hi"])
+    layer = max(1, int(np.prod(np.ceil((hi - lo)[:2] / h))))
+    hi[2] += extra_cells / layer * h
+    sc = dict(sc, config=dict(c, domain_hi=tuple(hi)))
+    p = sc["particles"]
+    out = W._particles(np.concatenate([p["pos"], [hi + 1.0]]), np.append(p["radius"], 1e-3),
+                       np.concatenate([p["vel"], np.zeros((1, 3))]),
+                       np.concatenate([p["omega"], np.zeros((1, 3))]))
+    sc = dict(sc, particles=out)
+    g, o = Dem.from_scene(sc), oracle_from_scene(sc)
+    g.step(7)
+    o.step(7)
+    gp, gd, gt = g.get_contacts()
+    op, od, ot = o.contacts()
+    assert np.array_equal(gp, op) and np.array_equal(gt, ot)
+    st = g.get_state()
+    assert not st["active"][n] and st["active"][:n].all()
+    # a context too large for one workgroup holds the same instance: same bits
+    rest = W.dense_snapshot(n=5000, seed=2, K=3, walls=False)
+    b = Dem.from_scenes([rest, sc])
+    b.step(7)
+    for k, v in st.items():
+        assert np.array_equal(v, b.get_state(1)[k]), k
+    for x, y in zip(g.get_contacts(), b.get_contacts(1)):
+        assert np.array_equal(x, y)
+    g.close()
+    b.close()
