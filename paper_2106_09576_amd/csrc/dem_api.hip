@@ -97,6 +97,8 @@ struct dem_ctx {
 
   std::vector<void*> allocs;
   std::vector<size_t> alloc_bytes;
+  // requests of a commit under way, placed in one allocation (reserve, place_reserved)
+  std::vector<std::pair<void**, size_t>> reserved;
   size_t dev_bytes = 0;
   int force_block = kBlock;  // threads per force workgroup (64, 128, 256)
   double cell_factor = 0.0;  // cell edge / d_max of the grids in use
@@ -192,7 +194,43 @@ int dalloc(dem_ctx* c, void** p, size_t bytes) {
   return DEM_OK;
 }
 
-// Free one allocation made by dalloc (after the stream has drained).
+template <typename T>
+int dalloc_t(dem_ctx* c, T** p, size_t count) {
+  return dalloc(c, (void**)p, count * sizeof(T));
+}
+
+// A commit's buffers come out of one allocation: some fifty of them cost 3 ms
+// to allocate and 4.7 ms to free one by one, a quarter of building a context
+// of 100,000 spheres.  reserve_t notes a request, place_reserved allocates for
+// all of them and sets their pointers.  They start on 2 MiB boundaries as soon
+// as they are that large, as allocations of their own do.
+template <typename T>
+void reserve_t(dem_ctx* c, T** p, size_t count) {
+  *p = nullptr;
+  c->reserved.emplace_back((void**)p, std::max<size_t>(count * sizeof(T), 256));
+}
+
+int place_reserved(dem_ctx* c) {
+  auto aligned = [](size_t at, size_t bytes) {
+    const size_t to = bytes >= (2u << 20) ? (2u << 20) : 256;
+    return (at + to - 1) / to * to;
+  };
+  size_t total = 0;
+  for (const auto& r : c->reserved) total = aligned(total, r.second) + r.second;
+  void* base = nullptr;
+  const int rc = total > 0 ? dalloc(c, &base, total) : DEM_OK;
+  size_t at = 0;
+  for (const auto& r : c->reserved) {
+    at = aligned(at, r.second);
+    if (rc == DEM_OK) *r.first = (char*)base + at;
+    at += r.second;
+  }
+  c->reserved.clear();
+  return rc;
+}
+
+// Free one allocation made by dalloc (after the stream has drained); part of a
+// commit's allocation stays until that is freed.
 void dfree(dem_ctx* c, void* p) {
   if (!p) return;
   for (size_t k = 0; k < c->allocs.size(); ++k)
@@ -203,11 +241,6 @@ void dfree(dem_ctx* c, void* p) {
       c->alloc_bytes.erase(c->alloc_bytes.begin() + (long)k);
       return;
     }
-}
-
-template <typename T>
-int dalloc_t(dem_ctx* c, T** p, size_t count) {
-  return dalloc(c, (void**)p, count * sizeof(T));
 }
 
 void destroy_graphs(dem_ctx* c) {
@@ -1162,8 +1195,8 @@ void plan_search_blocks(dem_ctx* c) {
 // Morton code interleaves the bits of its coordinates (bit l of axis a goes
 // to the next free code bit, levels l = 0, 1, ... and axes x, y, z in turn,
 // an axis dropping out once its bits are used up); its key is its rank by
-// that code among the grid's cells.  The tables live at c->d_ckey; hkeycell
-// (at c->d_key_cell) is the inverse, key -> cell, both over all instances.
+// that code among the grid's cells.  The tables go to c->d_ckey; hkeycell
+// (for c->d_key_cell) is the inverse, key -> cell, both over all instances.
 // hblocks: the search blocks (StepParams::sb_bits) of every grid, in key order.
 void grid_tables(dem_ctx* c, std::vector<uint32_t>* hckey, std::vector<uint32_t>* hkeycell,
                  std::vector<InstDev>* hinst, std::vector<SearchBlock>* hblocks) {
@@ -1172,7 +1205,6 @@ void grid_tables(dem_ctx* c, std::vector<uint32_t>* hckey, std::vector<uint32_t>
   hkeycell->clear();
   hblocks->clear();
   hinst->assign((size_t)B, InstDev{});
-  std::vector<std::pair<uint64_t, uint32_t>> code;
   for (int b = 0; b < B; ++b) {
     Instance& I = c->inst[(size_t)b];
     GridDev& g = I.grid;
@@ -1181,49 +1213,66 @@ void grid_tables(dem_ctx* c, std::vector<uint32_t>* hckey, std::vector<uint32_t>
       bits[a] = 0;
       while ((1 << bits[a]) < g.nc[a]) ++bits[a];
     }
-    int pos_of[3][32];
-    int next = 0;
+    // which bit of which axis each code bit is, from the lowest
+    struct Bit {
+      int axis, value;
+    };
+    std::vector<Bit> order;
     const int maxb = std::max(bits[0], std::max(bits[1], bits[2]));
     for (int lvl = 0; lvl < maxb; ++lvl)
       for (int a = 0; a < 3; ++a)
-        if (lvl < bits[a]) pos_of[a][lvl] = next++;
-    std::vector<uint64_t> spread[3];
-    for (int a = 0; a < 3; ++a) {
-      spread[a].resize((size_t)g.nc[a]);
-      for (int ci = 0; ci < g.nc[a]; ++ci) {
-        uint64_t m = 0;
-        for (int lvl = 0; lvl < bits[a]; ++lvl)
-          if ((ci >> lvl) & 1) m |= uint64_t(1) << pos_of[a][lvl];
-        spread[a][(size_t)ci] = m;
-      }
+        if (lvl < bits[a]) order.push_back(Bit{a, 1 << lvl});
+    // the cells that the lowest (at most 6) code bits tell apart, in order
+    const int low = std::min((int)order.size(), 6);
+    int off[64][3];
+    for (int m = 0; m < (1 << low); ++m) {
+      off[m][0] = off[m][1] = off[m][2] = 0;
+      for (int t = 0; t < low; ++t)
+        if ((m >> t) & 1) off[m][order[(size_t)t].axis] |= order[(size_t)t].value;
     }
-    // (code, linear index) of every cell, x fastest; sorted by code they are
-    // in Morton order
+    // a search block's cells share all but the lowest code bits
+    int sb = 0;
+    for (int a = 0; a < 3; ++a) sb += std::min(bits[a], c->sp.sb_bits[a]);
     const size_t base = hckey->size(), cells = (size_t)g.n_keys;
-    code.resize(cells);
-    size_t lin = 0;
-    for (int z = 0; z < g.nc[2]; ++z)
-      for (int y = 0; y < g.nc[1]; ++y)
-        for (int x = 0; x < g.nc[0]; ++x, ++lin)
-          code[lin] = {spread[0][(size_t)x] | spread[1][(size_t)y] | spread[2][(size_t)z],
-                       (uint32_t)lin};
-    std::sort(code.begin(), code.end());
     hckey->resize(base + cells);
     hkeycell->resize(base + cells);
-    // a search block's cells share all but the lowest code bits
-    int low = 0;
-    for (int a = 0; a < 3; ++a) low += std::min(bits[a], c->sp.sb_bits[a]);
-    for (size_t r = 0; r < cells; ++r) {
-      const uint32_t lin = code[r].second;
-      (*hckey)[base + lin] = (uint32_t)r;
-      (*hkeycell)[base + r] = (uint32_t)(base + lin);
-      if (r == 0 || (code[r].first >> low) != (code[r - 1].first >> low))
-        hblocks->push_back(SearchBlock{I.key_base + (uint32_t)r, 0, b, (int)(lin % (uint32_t)g.nc[0]),
-                                       (int)(lin / (uint32_t)g.nc[0] % (uint32_t)g.nc[1]),
-                                       (int)(lin / (uint32_t)g.nc[0] / (uint32_t)g.nc[1])});
-      hblocks->back().ncell += 1;
+    // Go through the codes in order (cells outside the grid drop out, whole
+    // ranges of them at a time): from a corner, the upper code bits are counted
+    // up like an odometer.  The rank of a cell in this order is its key.
+    uint32_t r = 0;
+    int x[3] = {0, 0, 0};
+    const int up = (int)order.size() - low;
+    std::vector<char> digit((size_t)up, 0);
+    for (;;) {
+      int block = -1;
+      for (int m = 0; m < (1 << low); ++m) {
+        const int cx = x[0] + off[m][0], cy = x[1] + off[m][1], cz = x[2] + off[m][2];
+        if (cx >= g.nc[0] || cy >= g.nc[1] || cz >= g.nc[2]) continue;
+        const uint32_t lin = (uint32_t)((cz * g.nc[1] + cy) * g.nc[0] + cx);
+        (*hckey)[base + lin] = r;
+        (*hkeycell)[base + r] = (uint32_t)(base + lin);
+        if ((m >> sb) != block) {
+          block = m >> sb;
+          hblocks->push_back(SearchBlock{I.key_base + r, 0, b, cx, cy, cz});
+        }
+        hblocks->back().ncell += 1;
+        ++r;
+      }
+      // next corner inside the grid
+      int t = 0;
+      for (; t < up; ++t) {
+        const Bit& d = order[(size_t)(low + t)];
+        if (digit[(size_t)t]) {
+          digit[(size_t)t] = 0;
+          x[d.axis] -= d.value;
+        } else if (x[d.axis] + d.value < g.nc[d.axis]) {
+          digit[(size_t)t] = 1;
+          x[d.axis] += d.value;
+          break;
+        }
+      }
+      if (t == up) break;
     }
-    g.ckey = c->d_ckey + base;
     InstDev& D = (*hinst)[(size_t)b];
     D.grid = g;
     D.key_base = I.key_base;
@@ -1240,6 +1289,15 @@ void grid_tables(dem_ctx* c, std::vector<uint32_t>* hckey, std::vector<uint32_t>
     // in d^2, below 4e-6
     D.ih = 1.0 / g.h;
     D.near2 = (float)(I.rs * I.rs * D.ih * D.ih + 4e-6) * 1.000001f;
+  }
+}
+
+// The grids' key tables at c->d_ckey, once that is allocated.
+void point_grids(dem_ctx* c, std::vector<InstDev>* hinst) {
+  size_t base = 0;
+  for (size_t b = 0; b < c->inst.size(); ++b) {
+    c->inst[b].grid.ckey = (*hinst)[b].grid.ckey = c->d_ckey + base;
+    base += (size_t)c->inst[b].grid.n_keys;
   }
 }
 
@@ -1281,6 +1339,7 @@ int regrid(dem_ctx* c, double cf) {
   std::vector<SearchBlock> hblocks;
   plan_search_blocks(c);
   grid_tables(c, &hckey, &hkeycell, &hinst, &hblocks);
+  point_grids(c, &hinst);
   c->n_blocks = (int)hblocks.size();
   rc = dalloc_t(c, &c->d_blocks, std::max<size_t>(hblocks.size(), 1));
   rc = rc ? rc : dalloc_t(c, &c->d_occupied, hblocks.size() + 1);
@@ -1417,58 +1476,69 @@ int commit(dem_ctx* c) {
     sp.drift_words *= 2;
   sp.drift_scale = ihs_min == ihs_max ? c->cfg.dt * ihs_max : 0.0;
 
+  // cell-key tables, search blocks and instance table
+  std::vector<uint32_t> hckey, hkeycell;
+  std::vector<InstDev> hinst;
+  std::vector<SearchBlock> hblocks;
+  plan_search_blocks(c);
+  grid_tables(c, &hckey, &hkeycell, &hinst, &hblocks);
+  c->n_blocks = (int)hblocks.size();
+
   // allocations
   const size_t NN = (size_t)std::max<int64_t>(N, 1);
-  int rc = DEM_OK;
-  for (int b = 0; b < 2 && rc == DEM_OK; ++b) {
-    rc = rc ? rc : dalloc_t(c, &c->pos[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->vel[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->omg[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->gid[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->info[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->F[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->T[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->wid[b], NN * kWallSlots);
-    rc = rc ? rc : dalloc_t(c, &c->whist[b], NN * kWallSlots * 3);
-    rc = rc ? rc : dalloc_t(c, &c->nbr[b], (size_t)std::max<int64_t>(c->cap, 1));
-    rc = rc ? rc : dalloc_t(c, &c->hist[b], (size_t)std::max<int64_t>(c->cap, 1) * 3);
-    rc = rc ? rc : dalloc_t(c, &c->rowlen[b], NN);
-    rc = rc ? rc : dalloc_t(c, &c->rowcut[b], NN);
+  for (int b = 0; b < 2; ++b) {
+    reserve_t(c, &c->pos[b], NN);
+    reserve_t(c, &c->vel[b], NN);
+    reserve_t(c, &c->omg[b], NN);
+    reserve_t(c, &c->gid[b], NN);
+    reserve_t(c, &c->info[b], NN);
+    reserve_t(c, &c->F[b], NN);
+    reserve_t(c, &c->T[b], NN);
+    reserve_t(c, &c->wid[b], NN * kWallSlots);
+    reserve_t(c, &c->whist[b], NN * kWallSlots * 3);
+    reserve_t(c, &c->nbr[b], (size_t)std::max<int64_t>(c->cap, 1));
+    reserve_t(c, &c->hist[b], (size_t)std::max<int64_t>(c->cap, 1) * 3);
+    reserve_t(c, &c->rowlen[b], NN);
+    reserve_t(c, &c->rowcut[b], NN);
   }
-  rc = rc ? rc : dalloc_t(c, &c->xref, NN);
-  rc = rc ? rc : dalloc_t(c, &c->keys, NN);
-  rc = rc ? rc : dalloc_t(c, &c->rank, NN);
-  rc = rc ? rc : dalloc_t(c, &c->count, (size_t)total_keys + 1);
-  rc = rc ? rc : dalloc_t(c, &c->start, (size_t)total_keys + 2);
-  rc = rc ? rc : dalloc_t(c, &c->tile_sums, (size_t)((total_keys + 1 + 1023) / 1024 + 1));
-  rc = rc ? rc : dalloc_t(c, &c->perm0, NN);
-  rc = rc ? rc : dalloc_t(c, &c->perm, NN);
-  rc = rc ? rc : dalloc_t(c, &c->inv, NN);
-  rc = rc ? rc : dalloc_t(c, &c->d_pp, (size_t)B * kMaxTypes * kMaxTypes);
-  rc = rc ? rc : dalloc_t(c, &c->d_pw, (size_t)B * kMaxTypes * kMaxTypes);
-  rc = rc ? rc : dalloc_t(c, &c->d_walls, (size_t)std::max(n_walls, 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_inst, (size_t)B);
-  rc = rc ? rc : dalloc_t(c, &c->d_flags, 1);
-  rc = rc ? rc : dalloc_t(c, &c->d_clock, 1);
-  rc = rc ? rc : dalloc_t(c, &c->d_stats, 4);
-  rc = rc ? rc : dalloc_t(c, &c->d_ckey, std::max<size_t>(ckey_total, 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_key_cell, std::max<size_t>(ckey_total, 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_cse, std::max<size_t>(ckey_total, 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_bound, (size_t)kBoundWords);
+  reserve_t(c, &c->xref, NN);
+  reserve_t(c, &c->keys, NN);
+  reserve_t(c, &c->rank, NN);
+  reserve_t(c, &c->count, (size_t)total_keys + 1);
+  reserve_t(c, &c->start, (size_t)total_keys + 2);
+  reserve_t(c, &c->tile_sums, (size_t)((total_keys + 1 + 1023) / 1024 + 1));
+  reserve_t(c, &c->perm0, NN);
+  reserve_t(c, &c->perm, NN);
+  reserve_t(c, &c->inv, NN);
+  reserve_t(c, &c->d_pp, (size_t)B * kMaxTypes * kMaxTypes);
+  reserve_t(c, &c->d_pw, (size_t)B * kMaxTypes * kMaxTypes);
+  reserve_t(c, &c->d_walls, (size_t)std::max(n_walls, 1));
+  reserve_t(c, &c->d_inst, (size_t)B);
+  reserve_t(c, &c->d_flags, 1);
+  reserve_t(c, &c->d_clock, 1);
+  reserve_t(c, &c->d_stats, 4);
+  reserve_t(c, &c->d_ckey, std::max<size_t>(ckey_total, 1));
+  reserve_t(c, &c->d_key_cell, std::max<size_t>(ckey_total, 1));
+  reserve_t(c, &c->d_cse, std::max<size_t>(ckey_total, 1));
+  reserve_t(c, &c->d_bound, (size_t)kBoundWords);
+  if (!htri.empty()) {
+    reserve_t(c, &c->d_tri, htri.size());
+    reserve_t(c, &c->d_mcell, hcell.size());
+    reserve_t(c, &c->d_mcell_tri, std::max<size_t>(hcell_tri.size(), 1));
+    for (int b = 0; b < 2; ++b) {
+      reserve_t(c, &c->mtri[b], NN * kMeshSlots);
+      reserve_t(c, &c->mhist[b], NN * kMeshSlots * 3);
+    }
+    reserve_t(c, &c->Fm, NN);
+    reserve_t(c, &c->Tm, NN);
+  }
+  reserve_t(c, &c->d_blocks, std::max<size_t>(hblocks.size(), 1));
+  reserve_t(c, &c->d_occupied, hblocks.size() + 1);
+  int rc = place_reserved(c);
+  // (an allocation of its own: it is freed when the record is disabled)
   if (c->record_pf)
     rc = rc ? rc : dalloc_t(c, &c->pair_force, (size_t)std::max<int64_t>(c->cap, 1) * 3);
-  if (!htri.empty()) {
-    rc = rc ? rc : dalloc_t(c, &c->d_tri, htri.size());
-    rc = rc ? rc : dalloc_t(c, &c->d_mcell, hcell.size());
-    rc = rc ? rc : dalloc_t(c, &c->d_mcell_tri, std::max<size_t>(hcell_tri.size(), 1));
-    for (int b = 0; b < 2; ++b) {
-      rc = rc ? rc : dalloc_t(c, &c->mtri[b], NN * kMeshSlots);
-      rc = rc ? rc : dalloc_t(c, &c->mhist[b], NN * kMeshSlots * 3);
-    }
-    rc = rc ? rc : dalloc_t(c, &c->Fm, NN);
-    rc = rc ? rc : dalloc_t(c, &c->Tm, NN);
-    c->has_mesh = rc == DEM_OK;
-  }
+  c->has_mesh = rc == DEM_OK && !htri.empty();
   if (rc == DEM_OK) {
     hipError_t he = hipHostMalloc((void**)&c->h_bound,
                                   sizeof(unsigned long long) * kBoundWords + kStageBytes,
@@ -1485,19 +1555,8 @@ int commit(dem_ctx* c) {
     return rc;
   }
 
-  // cell-key tables, instance table, walls and material-pair tables
-  std::vector<uint32_t> hckey, hkeycell;
-  std::vector<InstDev> hinst;
-  std::vector<SearchBlock> hblocks;
-  plan_search_blocks(c);
-  grid_tables(c, &hckey, &hkeycell, &hinst, &hblocks);
-  c->n_blocks = (int)hblocks.size();
-  rc = dalloc_t(c, &c->d_blocks, std::max<size_t>(hblocks.size(), 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_occupied, hblocks.size() + 1);
-  if (rc) {
-    free_particles(c);
-    return rc;
-  }
+  // the grids know where their keys are now; walls and material-pair tables
+  point_grids(c, &hinst);
   std::vector<WallDev> hwalls;
   std::vector<PairCoef> pp((size_t)B * kMaxTypes * kMaxTypes), pw(pp.size());
   memset(pp.data(), 0, pp.size() * sizeof(PairCoef));
