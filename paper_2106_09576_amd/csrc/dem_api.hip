@@ -121,6 +121,7 @@ struct dem_ctx {
   int* d_mcell_tri = nullptr;
   int* mtri[2]{};
   double* mhist[2]{};
+  int* mlist = nullptr;  // particles with triangle candidates
   double4 *Fm = nullptr, *Tm = nullptr;
   // per-contact force record (tests): three planes of cap doubles, or null
   bool record_pf = false;
@@ -279,6 +280,7 @@ void free_particles(dem_ctx* c) {
   c->d_mcell = c->d_mcell_tri = nullptr;
   c->mtri[0] = c->mtri[1] = nullptr;
   c->mhist[0] = c->mhist[1] = nullptr;
+  c->mlist = nullptr;
   c->Fm = c->Tm = nullptr;
   c->pair_force = nullptr;
   c->ready = false;
@@ -365,7 +367,7 @@ int64_t next_eval_rel(const dem_ctx* c) {
   return (c->cfg.integrator == 0 ? c->step + 1 : c->step) - c->host_base;
 }
 WallSlots wslots(dem_ctx* c, int k) { return WallSlots{c->wid[k], c->whist[k]}; }
-MeshSlots mslots(dem_ctx* c, int k) { return MeshSlots{c->mtri[k], c->mhist[k]}; }
+MeshSlots mslots(dem_ctx* c, int k) { return MeshSlots{c->mtri[k], c->mhist[k], c->mlist}; }
 MeshTables mtables(dem_ctx* c) { return MeshTables{c->d_tri, c->d_mcell, c->d_mcell_tri}; }
 
 // Contact search: counting sort into cells, reorder, particle-wall search and
@@ -393,6 +395,7 @@ int enqueue_rebuild(dem_ctx* c, int check_guard, int move_forces, int64_t step_r
     HIPCHK(launch_cell_rank(c->n, c->n_keys, c->perm0, c->keys, c->start, c->gid[p],
                             c->perm, s));
   }
+  if (c->has_mesh) HIPCHK(launch_fill_i32(c->mlist + c->n, 0, 1, s));
   HIPCHK(launch_reorder(c->sp, c->d_inst, c->perm, c->inv, pbufs(c, a), pbufs(c, a ^ 1),
                         c->gid[p],
                         c->gid[p ^ 1],
@@ -1529,6 +1532,7 @@ int commit(dem_ctx* c) {
       reserve_t(c, &c->mtri[b], NN * kMeshSlots);
       reserve_t(c, &c->mhist[b], NN * kMeshSlots * 3);
     }
+    reserve_t(c, &c->mlist, NN + 1);
     reserve_t(c, &c->Fm, NN);
     reserve_t(c, &c->Tm, NN);
   }

@@ -97,9 +97,12 @@ struct TriDev {
 
 // Particle-triangle candidates: slot s of particle i at s * n + i (global
 // triangle index or -1), tangential overlaps in 3 * kMeshSlots planes.
+// list: the particles that have candidates, in any order, their number at
+// list[n] (one copy: a search writes it).
 struct MeshSlots {
   int* tri;
   double* hist;
+  int* list;
 };
 
 // Triangle table and mesh grids (all null when no instance has a mesh).
