@@ -395,12 +395,12 @@ int enqueue_rebuild(dem_ctx* c, int check_guard, int move_forces, int64_t step_r
     HIPCHK(launch_cell_rank(c->n, c->n_keys, c->perm0, c->keys, c->start, c->gid[p],
                             c->perm, s));
   }
-  if (c->has_mesh) HIPCHK(launch_fill_i32(c->mlist + c->n, 0, 1, s));
+  if (c->has_mesh) HIPCHK(launch_fill_i32(c->mlist + c->n, 0, 2, s));
   HIPCHK(launch_reorder(c->sp, c->d_inst, c->perm, c->inv, pbufs(c, a), pbufs(c, a ^ 1),
                         c->gid[p],
                         c->gid[p ^ 1],
                         c->info[p], c->info[p ^ 1], c->xref, wslots(c, p), wslots(c, p ^ 1),
-                        c->d_walls, mtables(c), mslots(c, p), mslots(c, p ^ 1),
+                        c->d_walls, mtables(c), mslots(c, p), mslots(c, p ^ 1), c->rank,
                         move_forces ? c->F[p] : nullptr,
                         move_forces ? c->T[p] : nullptr, c->F[p ^ 1], c->T[p ^ 1],
                         c->d_clock, step_rel, bound_step_rel, c->d_flags, s));
@@ -986,7 +986,12 @@ int commit(dem_ctx* c);
 // reach of a candidate (largest radius + skin), every triangle listed in
 // the cells its own grown box overlaps (ascending triangle order), so that
 // the cell of a particle centre lists every triangle that can be its
-// candidate.  Sets the mesh fields of the instances' walls.
+// candidate.  kMeshPad, in cells, stands for the rounding of a position in the
+// moving mesh (1e-16 of the coordinates).  A whole cell in its place listed
+// every triangle in more than five times as many cells.  Sets the mesh fields of the
+// instances' walls.
+constexpr double kMeshPad = 1.0 / 64.0;
+
 int build_meshes(dem_ctx* c, std::vector<TriDev>* htri, std::vector<int>* hcell,
                  std::vector<int>* hcell_tri) {
   c->tri_wall.clear();
@@ -1061,8 +1066,8 @@ int build_meshes(dem_ctx* c, std::vector<TriDev>* htri, std::vector<int>* hcell,
         for (int k = 0; k < 3; ++k) {
           const double tl = std::min(T.p[0][k], std::min(T.p[1][k], T.p[2][k])) - reach;
           const double th = std::max(T.p[0][k], std::max(T.p[1][k], T.p[2][k])) + reach;
-          a[k] = std::max<int64_t>(0, (int64_t)floor((tl - W.mlo[k]) / mh) - 1);
-          b[k] = std::min<int64_t>(nc[k] - 1, (int64_t)floor((th - W.mlo[k]) / mh) + 1);
+          a[k] = std::max<int64_t>(0, (int64_t)floor((tl - W.mlo[k]) / mh - kMeshPad));
+          b[k] = std::min<int64_t>(nc[k] - 1, (int64_t)floor((th - W.mlo[k]) / mh + kMeshPad));
         }
         for (int64_t z = a[2]; z <= b[2]; ++z)
           for (int64_t y = a[1]; y <= b[1]; ++y)
@@ -1532,7 +1537,7 @@ int commit(dem_ctx* c) {
       reserve_t(c, &c->mtri[b], NN * kMeshSlots);
       reserve_t(c, &c->mhist[b], NN * kMeshSlots * 3);
     }
-    reserve_t(c, &c->mlist, NN + 1);
+    reserve_t(c, &c->mlist, NN + 2);
     reserve_t(c, &c->Fm, NN);
     reserve_t(c, &c->Tm, NN);
   }

@@ -254,12 +254,14 @@ hipError_t launch_sort_small(const InstDev* inst, const StepParams& sp, const do
 // are at time (*clock + step_rel) dt.
 // It also restarts the displacement bound (StepParams) for the force
 // evaluation at step *clock + bound_step_rel.
+// near_list: n words of scratch for contexts with meshes, whose two counts
+// (MeshSlots::list) are to be zero.
 hipError_t launch_reorder(const StepParams& sp, const InstDev* inst, const int* perm, int* inv,
                           ParticleBufs src,
                           ParticleBufs dst, const int* gid_src, int* gid_dst,
                           const int* info_src, int* info_dst, double4* xref,
                           WallSlots ws_src, WallSlots ws_dst, const WallDev* walls,
-                          MeshTables mt, MeshSlots ms_src, MeshSlots ms_dst,
+                          MeshTables mt, MeshSlots ms_src, MeshSlots ms_dst, int* near_list,
                           const double4* F_src, const double4* T_src, double4* F_dst,
                           double4* T_dst, const int64_t* clock, int64_t step_rel,
                           int64_t bound_step_rel, int* flags, hipStream_t s);

@@ -599,6 +599,18 @@ __device__ inline void tri_closest(const TriDev& T, const double vel[3], double 
   }
 }
 
+// the cell of mesh W's grid that x lies in at time t (-1: outside the grid)
+__device__ inline int mesh_cell(const WallDev& W, const double x[3], double t) {
+  int c3[3];
+  bool in = true;
+  for (int k = 0; k < 3; ++k) {
+    const double u = (x[k] - W.vel[k] * t - W.mlo[k]) / W.mh;
+    if (!(u >= 0.0 && u < (double)W.mnc[k])) in = false;
+    c3[k] = in ? (int)u : 0;
+  }
+  return in ? W.cell_base + c3[0] + W.mnc[0] * (c3[1] + W.mnc[1] * c3[2]) : -1;
+}
+
 // ----------------------------------------------------------------- reorder
 
 // Gather every particle array into sorted order, record the reference
@@ -610,7 +622,7 @@ __global__ void k_reorder(StepParams sp, const InstDev* __restrict__ inst,
                           int* __restrict__ gid_dst, const int* __restrict__ info_src,
                           int* __restrict__ info_dst, double4* __restrict__ xref,
                           WallSlots ws_src, WallSlots ws_dst, const WallDev* __restrict__ walls,
-                          MeshTables mt, MeshSlots ms_src, MeshSlots ms_dst,
+                          MeshTables mt, MeshSlots ms_dst, int* __restrict__ near_list,
                           const double4* __restrict__ F_src, const double4* __restrict__ T_src,
                           double4* __restrict__ F_dst, double4* __restrict__ T_dst,
                           const int64_t* __restrict__ clock, int64_t step_rel,
@@ -672,75 +684,125 @@ __global__ void k_reorder(StepParams sp, const InstDev* __restrict__ inst,
   }
   for (; c < kWallSlots; ++c) ws_dst.wid[(int64_t)c * n + p] = -1;
   if (!mt.tri) return;
-  // particle-triangle candidates: the triangles listed in the centre's cell
-  // of each mesh grid that lie less than R + skin away from it, with the
-  // centre less than R behind their plane; overlaps carried by triangle
-  int cm = 0;
+  // the particles whose cell lists a triangle, for k_mesh_find
+  for (int s = 0; s < kMeshSlots; ++s) ms_dst.tri[(int64_t)s * n + p] = -1;
   if (!(inf & kInactive)) {
     const InstDev& I = inst[inf >> kInstShift];
+    const double x[3] = {ps.x, ps.y, ps.z};
+    bool near = false;
+    for (int w = I.wall_begin; w < I.wall_end && !near; ++w) {
+      if (walls[w].kind != 3) continue;
+      const int cb = mesh_cell(walls[w], x, t);
+      near = cb >= 0 && mt.cell[cb] < mt.cell[cb + 1];
+    }
+    if (near) near_list[atomicAdd(ms_dst.list + n + 1, 1)] = p;
+  }
+}
+
+// Particle-triangle candidates of the sorted particles: the triangles listed
+// in the centre's cell of each mesh grid that lie less than R + skin away from
+// it, with the centre less than R behind their plane, in that order; overlaps
+// carried by triangle.
+//
+// Over the list of the particles whose cell lists a triangle (k_reorder), with
+// eight lanes each: they take the triangles of the cell eight at a time, and a
+// candidate's slot follows from the ballot of the lanes before it.  What
+// bounds it is a chain of dependent reads per particle (cell, triangle number,
+// triangle, old slots).  In a drum of 200,000 one thread per particle, in
+// k_reorder, took that to 143 us; eight lanes for every particle of the
+// context took 82 here and 14 there, the list 59 and 28, and with the tighter
+// lists of cells (build_meshes) 29 and 23.
+__global__ void __launch_bounds__(kBlock)
+k_mesh_find(StepParams sp, const InstDev* __restrict__ inst, const int* __restrict__ perm,
+            const int* __restrict__ near_list, const double4* __restrict__ pos,
+            const int* __restrict__ info,
+            const WallDev* __restrict__ walls, MeshTables mt, MeshSlots src, MeshSlots dst,
+            const int64_t* __restrict__ clock, int64_t step_rel, int* __restrict__ flags) {
+  static_assert(kMeshSlots == 8, "a lane per slot");
+  const int n = sp.n, count = dst.list[n + 1];
+  const int lane = threadIdx.x & 7, shift = threadIdx.x & 56;
+  for (int at = (int)(blockIdx.x * kBlock + threadIdx.x) >> 3; at < count;
+       at += (int)(gridDim.x * kBlock) >> 3) {
+    const int p = near_list[at];
+    const int o = perm[p];
+    const int inf = info[p];
+    const int old = src.tri[(int64_t)lane * n + o];
+    int cm = 0;
+    const InstDev& I = inst[inf >> kInstShift];
+    const double t = (double)(*clock + step_rel) * sp.dt;  // meshes where they are now
+    const double4 ps = pos[p];
     const double x[3] = {ps.x, ps.y, ps.z};
     const double R = ps.w;
     const double m = R + I.skin;
     for (int w = I.wall_begin; w < I.wall_end && cm <= kMeshSlots; ++w) {
       const WallDev& W = walls[w];
       if (W.kind != 3) continue;
-      int c3[3];
-      bool in = true;
-      for (int k = 0; k < 3; ++k) {
-        const double u = (x[k] - W.vel[k] * t - W.mlo[k]) / W.mh;
-        if (!(u >= 0.0 && u < (double)W.mnc[k])) in = false;
-        c3[k] = in ? (int)u : 0;
-      }
-      if (!in) continue;
-      const int cb = W.cell_base + c3[0] + W.mnc[0] * (c3[1] + W.mnc[1] * c3[2]);
+      const int cb = mesh_cell(W, x, t);
+      if (cb < 0) continue;
       const int q1 = mt.cell[cb + 1];
-      for (int q = mt.cell[cb]; q < q1; ++q) {
-        const int tr = mt.cell_tri[q];
-        TriGeo g;
-        tri_closest(mt.tri[tr], W.vel, t, x, g);
-        if (!(g.s > -R && g.d2 < m * m)) continue;
-        if (cm == kMeshSlots) {
-          atomicOr(flags, kFlagMeshOverflow);
-          ++cm;
+      for (int q = mt.cell[cb]; q < q1; q += 8) {
+        const int tr = q + lane < q1 ? mt.cell_tri[q + lane] : -1;
+        bool near = false;
+        if (tr >= 0) {
+          TriGeo g;
+          tri_closest(mt.tri[tr], W.vel, t, x, g);
+          near = g.s > -R && g.d2 < m * m;
+        }
+        const unsigned found = (unsigned)(__ballot(near) >> shift) & 0xffu;
+        if (found == 0u) continue;
+        int from = -1;  // the slot that had this triangle (a triangle is in one only)
+#pragma unroll
+        for (int s = 0; s < kMeshSlots; ++s)
+          if (__shfl(old, shift + s, 64) == tr) from = s;
+        const int slot = cm + __popc(found & ((1u << lane) - 1u));
+        if (near && slot < kMeshSlots) {
+          double h0 = 0.0, h1 = 0.0, h2 = 0.0;
+          if (from >= 0) {
+            h0 = src.hist[(int64_t)(3 * from + 0) * n + o];
+            h1 = src.hist[(int64_t)(3 * from + 1) * n + o];
+            h2 = src.hist[(int64_t)(3 * from + 2) * n + o];
+          }
+          dst.tri[(int64_t)slot * n + p] = tr;
+          dst.hist[(int64_t)(3 * slot + 0) * n + p] = h0;
+          dst.hist[(int64_t)(3 * slot + 1) * n + p] = h1;
+          dst.hist[(int64_t)(3 * slot + 2) * n + p] = h2;
+        }
+        cm += __popc(found);
+        if (cm > kMeshSlots) {
+          if (lane == 0) atomicOr(flags, kFlagMeshOverflow);
           break;
         }
-        double h0 = 0.0, h1 = 0.0, h2 = 0.0;
-        for (int s = 0; s < kMeshSlots; ++s) {
-          const int ot = ms_src.tri[(int64_t)s * n + o];
-          if (ot < 0) break;
-          if (ot == tr) {
-            h0 = ms_src.hist[(int64_t)(3 * s + 0) * n + o];
-            h1 = ms_src.hist[(int64_t)(3 * s + 1) * n + o];
-            h2 = ms_src.hist[(int64_t)(3 * s + 2) * n + o];
-            break;
-          }
-        }
-        ms_dst.tri[(int64_t)cm * n + p] = tr;
-        ms_dst.hist[(int64_t)(3 * cm + 0) * n + p] = h0;
-        ms_dst.hist[(int64_t)(3 * cm + 1) * n + p] = h1;
-        ms_dst.hist[(int64_t)(3 * cm + 2) * n + p] = h2;
-        ++cm;
       }
     }
+    if (lane >= cm) dst.tri[(int64_t)lane * n + p] = -1;
+    if (lane == 0 && cm > 0) dst.list[atomicAdd(dst.list + n, 1)] = p;
   }
-  for (int c2 = cm < kMeshSlots ? cm : kMeshSlots; c2 < kMeshSlots; ++c2)
-    ms_dst.tri[(int64_t)c2 * n + p] = -1;
-  if (cm > 0) ms_dst.list[atomicAdd(ms_dst.list + n, 1)] = p;
+}
+
+// Workgroups of 32 particles each: enough to keep the chip busy, and no more
+// than a context can need.
+static unsigned mesh_grid(int n) {
+  const int64_t b = ((int64_t)n + 31) / 32;
+  return (unsigned)(b < 2048 ? b : 2048);
 }
 
 hipError_t launch_reorder(const StepParams& sp, const InstDev* inst, const int* perm, int* inv,
                           ParticleBufs src, ParticleBufs dst, const int* gid_src, int* gid_dst,
                           const int* info_src, int* info_dst, double4* xref,
                           WallSlots ws_src, WallSlots ws_dst, const WallDev* walls,
-                          MeshTables mt, MeshSlots ms_src, MeshSlots ms_dst,
+                          MeshTables mt, MeshSlots ms_src, MeshSlots ms_dst, int* near_list,
                           const double4* F_src, const double4* T_src, double4* F_dst,
                           double4* T_dst, const int64_t* clock, int64_t step_rel,
                           int64_t bound_step_rel, int* flags, hipStream_t s) {
   hipLaunchKernelGGL(k_reorder, dim3(grid_for(sp.n)), dim3(kBlock), 0, s, sp, inst, perm, inv,
                      src, dst,
-                     gid_src, gid_dst, info_src, info_dst, xref, ws_src, ws_dst, walls, mt,
-                     ms_src, ms_dst, F_src, T_src, F_dst, T_dst, clock, step_rel,
-                     bound_step_rel, flags);
+                     gid_src, gid_dst, info_src, info_dst, xref, ws_src, ws_dst, walls, mt, ms_dst,
+                     near_list, F_src, T_src, F_dst, T_dst, clock, step_rel, bound_step_rel,
+                     flags);
+  if (mt.tri)
+    hipLaunchKernelGGL(k_mesh_find, dim3(mesh_grid(sp.n)), dim3(kBlock), 0, s, sp, inst, perm,
+                       near_list, dst.pos, info_dst, walls, mt, ms_src, ms_dst, clock, step_rel,
+                       flags);
   return hipGetLastError();
 }
 
@@ -2151,13 +2213,6 @@ k_mesh(StepParams sp, const PairCoef* __restrict__ pwc, const WallDev* __restric
       Tm[i] = make_double4(FT[3], FT[4], FT[5], 0.0);
     }
   }
-}
-
-// Workgroups of 32 particles each: enough to keep the chip busy, and no more
-// than a context can need.
-static unsigned mesh_grid(int n) {
-  const int64_t b = ((int64_t)n + 31) / 32;
-  return (unsigned)(b < 2048 ? b : 2048);
 }
 
 hipError_t launch_mesh(int precision, const StepParams& sp, const PairCoef* pw,
