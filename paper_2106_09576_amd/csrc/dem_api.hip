@@ -428,6 +428,31 @@ int enqueue_force(dem_ctx* c, int mode, int64_t step_rel) {
   return DEM_OK;
 }
 
+// `count` steps of mode 0 or 2.  Contexts that one workgroup can hold take them
+// in launches of up to kStepsPerLaunch steps (bounded, so that a launch stays
+// short next to other work on the device).
+constexpr int64_t kStepsPerLaunch = 256;
+
+int enqueue_forces(dem_ctx* c, int mode, int64_t count, int64_t step_rel) {
+  const bool whole = c->n <= kStepsMax && !c->has_mesh && !c->pair_force;
+  for (int64_t j = 0; j < count;) {
+    if (!whole) {
+      if (int rc = enqueue_force(c, mode, step_rel + j)) return rc;
+      ++j;
+      continue;
+    }
+    const int m = (int)std::min(count - j, kStepsPerLaunch);
+    const int a = c->cur, b = a ^ (m & 1), p = c->pcur;
+    HIPCHK(launch_force_steps(mode, c->cfg.precision, c->sp, c->d_inst, c->d_pp, c->d_pw,
+                              c->d_walls, pbufs(c, a), pbufs(c, b), c->info[p], nlist(c, p),
+                              wslots(c, p), c->F[p], c->T[p], c->d_clock, step_rel + j, m,
+                              c->d_flags, c->pair_mode, c->stream));
+    c->cur = b;
+    j += m;
+  }
+  return DEM_OK;
+}
+
 int timed_begin(dem_ctx* c, int kind) {
   if (!c->timing) return DEM_OK;
   hipEvent_t e;
@@ -487,6 +512,14 @@ int eager_force(dem_ctx* c, int mode, int64_t step_rel) {
   return timed_end(c);
 }
 
+// (timed one by one when timing is on)
+int eager_forces(dem_ctx* c, int mode, int64_t count, int64_t step_rel) {
+  if (!c->timing) return enqueue_forces(c, mode, count, step_rel);
+  for (int64_t j = 0; j < count; ++j)
+    if (int rc = eager_force(c, mode, step_rel + j)) return rc;
+  return DEM_OK;
+}
+
 int set_clock(dem_ctx* c, int64_t value) {
   if (c->host_base != value) {
     HIPCHK(launch_tick(c->d_clock, value - c->host_base, c->stream));
@@ -509,10 +542,10 @@ int get_chunk_graph(dem_ctx* c, hipGraphExec_t* out) {
   int rc = DEM_OK;
   if (c->cfg.integrator == 0) {
     rc = enqueue_rebuild(c, 1, 0, 0);
-    for (int j = 0; j < K && rc == DEM_OK; ++j) rc = enqueue_force(c, 0, j);
+    if (rc == DEM_OK) rc = enqueue_forces(c, 0, K, 0);
   } else {
     // Euler: the search follows the K updates, at the time of the last
-    for (int j = 0; j < K && rc == DEM_OK; ++j) rc = enqueue_force(c, 2, j);
+    rc = enqueue_forces(c, 2, K, 0);
     if (rc == DEM_OK) rc = enqueue_rebuild(c, 1, move_forces_at_search(c), K);
   }
   if (rc == DEM_OK) {
@@ -585,18 +618,12 @@ int launch_chunk(dem_ctx* c, int64_t clock_at_start) {
 // per-step maxima are read back.  The displacement guard of every search
 // still checks the true displacement.
 
-int enqueue_dyn_chunk(dem_ctx* c, int L, bool search, bool last_is_call_end) {
-  const int vv = c->cfg.integrator == 0;
+int enqueue_dyn_chunk(dem_ctx* c, int L, bool search) {
   if (search) {
     int rc = enqueue_rebuild(c, 1, move_forces_at_search(c), 0);
     if (rc) return rc;
   }
-  for (int j = 0; j < L; ++j) {
-    const int mode = vv ? ((last_is_call_end && j == L - 1) ? 1 : 0) : 2;
-    int rc = enqueue_force(c, mode, j);
-    if (rc) return rc;
-  }
-  return DEM_OK;
+  return enqueue_forces(c, c->cfg.integrator == 0 ? 0 : 2, L, 0);
 }
 
 int get_dyn_graph(dem_ctx* c, bool search, hipGraphExec_t* out) {
@@ -608,7 +635,7 @@ int get_dyn_graph(dem_ctx* c, bool search, hipGraphExec_t* out) {
   const int save_cur = c->cur, save_pcur = c->pcur;
   const int64_t save_rb = c->n_rebuilds;
   HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-  int rc = enqueue_dyn_chunk(c, kDynChunk, search, false);
+  int rc = enqueue_dyn_chunk(c, kDynChunk, search);
   if (rc == DEM_OK) {
     hipError_t e = launch_tick(c->d_clock, kDynChunk, c->stream);
     if (e != hipSuccess) rc = set_err(DEM_EHIP, "tick launch: %s", hipGetErrorString(e));
@@ -729,10 +756,9 @@ int step_dynamic(dem_ctx* c, int64_t n_steps) {
       // eager: the clock stays, the step offset is explicit
       const int64_t base = (vv ? s : s - 1) - c->host_base;
       if (search && (rc = eager_rebuild(c, base))) return rc;
-      for (int j = 0; j < L; ++j) {
-        const int mode = vv ? ((call_end && j == L - 1) ? 1 : 0) : 2;
-        if ((rc = eager_force(c, mode, base + j))) return rc;
-      }
+      const int last = vv && call_end ? 1 : 0;  // a call's last Verlet step has its own mode
+      if ((rc = eager_forces(c, vv ? 0 : 2, L - last, base))) return rc;
+      if (last && (rc = eager_force(c, 1, base + L - 1))) return rc;
     }
     // the chunk evaluated the forces at x^e0 .. x^(e0 + L - 1); the last force
     // launch of a Verlet call does not drift
@@ -2132,8 +2158,15 @@ int dem_step(dem_ctx* c, int64_t n_steps) {
         continue;
       }
       if (s % K == 0 && (rc = eager_rebuild(c, s - c->host_base))) return rc;
-      if ((rc = eager_force(c, s < s_end ? 0 : 1, s - c->host_base))) return rc;
-      s += 1;
+      // the steps before the next search; the call's last has its own mode
+      const int64_t next = std::min((s / K + 1) * K, s_end);
+      if (s < next) {
+        if ((rc = eager_forces(c, 0, next - s, s - c->host_base))) return rc;
+        s = next;
+      } else {
+        if ((rc = eager_force(c, 1, s - c->host_base))) return rc;
+        s += 1;
+      }
     }
   } else {
     int64_t s = s0 + 1;
@@ -2143,7 +2176,9 @@ int dem_step(dem_ctx* c, int64_t n_steps) {
         s += K;
         continue;
       }
-      if ((rc = eager_force(c, 2, (s - 1) - c->host_base))) return rc;
+      const int64_t next = std::min((s + K - 1) / K * K, s_end);
+      if ((rc = eager_forces(c, 2, next - s + 1, (s - 1) - c->host_base))) return rc;
+      s = next;
       if (s % K == 0 && (rc = eager_rebuild(c, s - c->host_base))) return rc;
       s += 1;
     }

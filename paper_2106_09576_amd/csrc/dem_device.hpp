@@ -293,6 +293,15 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
                         double4* F, double4* T, const int64_t* clock, int64_t step_rel,
                         const int* flags, const int* xsel, const double4* Fx, const double4* Tx,
                         double* pf, int block, int pair_mode, hipStream_t s);
+// `steps` launches of mode 0 or 2 as one, for contexts of at most kStepsMax
+// particles without meshes: the state ends in `out`, which may be `in`.
+constexpr int kStepsMax = 128;
+hipError_t launch_force_steps(int mode, int precision, const StepParams& sp, const InstDev* inst,
+                              const PairCoef* pp, const PairCoef* pw, const WallDev* walls,
+                              ParticleBufs in, ParticleBufs out, const int* info, NbrList l,
+                              WallSlots ws, double4* F, double4* T, const int64_t* clock,
+                              int64_t step_rel, int steps, const int* flags, int pair_mode,
+                              hipStream_t s);
 // Contacts of the particles with triangle candidates at time (*clock +
 // step_rel) dt (tangential overlaps updated): their force and torque into
 // Fm / Tm (written for those particles only).

@@ -1692,6 +1692,33 @@ struct Tile {
   }
 };
 
+// The states of a context that one workgroup holds as a whole (k_force_steps).
+struct TileAll {
+  double4* rec;
+  int* in;
+  static constexpr int lo = 0;
+  __device__ __forceinline__ double4 pos(const ParticleBufs&, int j) const { return rec[3 * j]; }
+  __device__ __forceinline__ double4 vel(const ParticleBufs&, int j) const { return rec[3 * j + 1]; }
+  __device__ __forceinline__ double4 omg(const ParticleBufs&, int j) const { return rec[3 * j + 2]; }
+  __device__ __forceinline__ int info(const int* __restrict__, int j) const { return in[j]; }
+};
+
+// Where the updated state of particle i goes: the context's other buffers, or
+// a workgroup's records.
+template <bool NT>
+struct ToBufs {
+  ParticleBufs b;
+  __device__ __forceinline__ void pos(int i, const double4& v) const { st_own<NT>(v, b.pos + i); }
+  __device__ __forceinline__ void vel(int i, const double4& v) const { st_own<NT>(v, b.vel + i); }
+  __device__ __forceinline__ void omg(int i, const double4& v) const { st_own<NT>(v, b.omg + i); }
+};
+struct ToRecords {
+  double4* rec;
+  __device__ __forceinline__ void pos(int i, const double4& v) const { rec[3 * i] = v; }
+  __device__ __forceinline__ void vel(int i, const double4& v) const { rec[3 * i + 1] = v; }
+  __device__ __forceinline__ void omg(int i, const double4& v) const { rec[3 * i + 2] = v; }
+};
+
 // Square of a step's drift |v| dt in units of half the skin: scale = dt * 2 /
 // skin.  Maxima of squares are taken on the device, the root on the host.
 __device__ __forceinline__ double drift2(const double4& v, double scale) {
@@ -1708,11 +1735,12 @@ __device__ __forceinline__ double drift_scale(const StepParams& sp,
 // Forces on particle i and its integration; returns the squared drift of
 // this step in units of half the instance's skin (for the dynamic search
 // trigger) when asked for it.
-template <typename R, int MODE, int MODEL, typename WAY, bool REC, int PAIRS, typename TileT>
+template <typename R, int MODE, int MODEL, typename WAY, bool REC, int PAIRS, typename TileT,
+          typename OutT>
 __device__ __forceinline__ double force_particle(
     const int i, const int g, const StepParams& sp, const InstDev* __restrict__ inst,
     const PairCoef* __restrict__ ppc, const PairCoef* __restrict__ pwc,
-    const WallDev* __restrict__ walls, ParticleBufs in, ParticleBufs out,
+    const WallDev* __restrict__ walls, ParticleBufs in, const OutT& out,
     const int* __restrict__ info, NbrList l, WallSlots ws, double4* __restrict__ Fo,
     double4* __restrict__ To, const int64_t* __restrict__ clock, int64_t step_rel,
     const int* __restrict__ flags, const bool want_drift, const int* __restrict__ xsel,
@@ -1728,9 +1756,9 @@ __device__ __forceinline__ double force_particle(
   // frozen after an error, and for inactive particles: carry the state over
   if ((inf & kInactive) || *flags != 0) {
     if (g != 0) return 0.0;
-    out.pos[i] = xi;
-    out.vel[i] = tile.rec[own + 1];
-    out.omg[i] = tile.rec[own + 2];
+    out.pos(i, xi);
+    out.vel(i, tile.rec[own + 1]);
+    out.omg(i, tile.rec[own + 2]);
     if (MODE != 0) {
       Fo[i] = make_double4(0.0, 0.0, 0.0, 0.0);
       To[i] = make_double4(0.0, 0.0, 0.0, 0.0);
@@ -1906,14 +1934,30 @@ __device__ __forceinline__ double force_particle(
       if (want_drift) drift = drift2(vi, drift_scale(sp, inst, inf));
     }
   }
-  if (g == 0) st_own<WAY::kStateNt>(xi, out.pos + i);
-  if (g == 1 % G) st_own<WAY::kStateNt>(vi, out.vel + i);
-  if (g == 2 % G) st_own<WAY::kStateNt>(wi, out.omg + i);
+  if (g == 0) out.pos(i, xi);
+  if (g == 1 % G) out.vel(i, vi);
+  if (g == 2 % G) out.omg(i, wi);
   if (MODE != 0 && g == 3 % G) {
     Fo[i] = make_double4(F[0], F[1], F[2], 0.0);
     To[i] = make_double4(T[0], T[1], T[2], 0.0);
   }
   return drift;
+}
+
+// The row cut that a displacement bound of acc half skins allows, the same in
+// every lane (a relative margin of 1e-6 covers every rounding of the bound and
+// of the gaps), and the row length that it leaves.
+__device__ __forceinline__ int row_cut(double acc) {
+  const double accm = acc * (1.0 + 1e-6);
+  const int u = accm < kCutFrac[0] ? 0 : (accm < kCutFrac[1] ? 1 : (accm < kCutFrac[2] ? 2 : 3));
+  return __builtin_amdgcn_readfirstlane(u);
+}
+__device__ __forceinline__ int cut_row(int len, int cut, int u_cut) {
+  if (u_cut < 3) {
+    const int c = (cut >> (kCutBits * u_cut)) & kCutMask;
+    if (c != kCutMask && c < len) return c;
+  }
+  return len;
 }
 
 // Occupancy floor: four wavefronts per SIMD (128 VGPRs, no spills), except
@@ -1951,8 +1995,7 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
   }
   // displacement bound of x^step since the last search (half skins): the
   // previous evaluation's bound plus the largest drift of the update since;
-  // then the row cut it allows (uniform across the wavefront; a relative
-  // margin of 1e-6 covers every rounding of the bound and of the gaps)
+  // then the row cut it allows
   int u_cut;
   {
     const double m = sqrt(drift_of(sp, sp.brec + bound_slot(step, 0) * kDriftRec));
@@ -1964,14 +2007,9 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
         sp.blog[step & (kDriftLog - 1)] = m;
       }
     }
-    const double accm = acc * (1.0 + 1e-6);
-    u_cut = accm < kCutFrac[0] ? 0 : (accm < kCutFrac[1] ? 1 : (accm < kCutFrac[2] ? 2 : 3));
-    u_cut = __builtin_amdgcn_readfirstlane(u_cut);
+    u_cut = row_cut(acc);
   }
-  if (u_cut < 3) {
-    const int c = (cut >> (kCutBits * u_cut)) & kCutMask;
-    if (c != kCutMask && c < len) len = c;
-  }
+  len = cut_row(len, cut, u_cut);
   extern __shared__ double4 force_lds[];
   Tile<G> tile;
   tile.rec = force_lds;
@@ -1982,11 +2020,91 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
   __syncthreads();
   double d = 0.0;
   if (i < sp.n)
-    d = force_particle<R, MODE, MODEL, WAY, REC, PAIRS>(i, g, sp, inst, ppc, pwc, walls, in, out, info,
-                                                  l, ws, Fo, To, clock, step_rel, flags,
+    d = force_particle<R, MODE, MODEL, WAY, REC, PAIRS>(i, g, sp, inst, ppc, pwc, walls, in,
+                                                  ToBufs<WAY::kStateNt>{out}, info, l, ws, Fo, To, clock, step_rel, flags,
                                                   MODE != 1, xsel, Fx, Tx, tile, len, jr0, pf);
   // this launch's own update produced x^(step + 1)
   if (MODE != 1) raise_drift(sp, sp.brec + bound_slot(step, 1) * kDriftRec, d);
+}
+
+// `steps` steps of a context of at most kStepsMax particles in one workgroup:
+// the updated states stay in LDS, in two copies that take turns, and the drift
+// of a step is reduced there, so that a barrier stands where the end of one
+// launch and the start of the next were.  Row entries and histories stay in
+// their buffers (a lane reads back only what it wrote).  What is left is one
+// particle's chain of loads and arithmetic: 2.7 us per step for 20 spheres,
+// where a launch took 4.2 and 1.1 passed between two.  Registers for the two
+// wavefronts per SIMD of the largest context.
+template <typename R, int MODE, int MODEL, int PAIRS>
+__global__ void __launch_bounds__(4 * kStepsMax) __attribute__((amdgpu_waves_per_eu(2)))
+k_force_steps(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restrict__ ppc,
+              const PairCoef* __restrict__ pwc, const WallDev* __restrict__ walls,
+              ParticleBufs in, ParticleBufs out, const int* __restrict__ info, NbrList l,
+              WallSlots ws, double4* __restrict__ Fo, double4* __restrict__ To,
+              const int64_t* __restrict__ clock, int64_t step_rel, int steps,
+              const int* __restrict__ flags) {
+  typedef WaySmall4 WAY;
+  constexpr int G = WAY::kLanes, kPerWave = 64 / G;
+  __shared__ double wave_drift[2][4 * kStepsMax / 64];
+  extern __shared__ double4 force_lds[];
+  const int nb = blockDim.x / G, waves = blockDim.x >> 6, wave = threadIdx.x >> 6;
+  const int g = (threadIdx.x & 63) / kPerWave;
+  const int i = wave * kPerWave + (threadIdx.x & (kPerWave - 1));
+  const int n = sp.n;
+  const int64_t step0 = *clock + step_rel;
+  int len_all = 0, cut = 0;
+  if (i < n) {
+    len_all = l.rowlen[i];
+    cut = l.rowcut[i];
+  }
+  double m = sqrt(drift_of(sp, sp.brec + bound_slot(step0, 0) * kDriftRec));
+  double acc = sp.bacc[bound_slot(step0, -1)];
+  Tile<G> first;
+  first.rec = force_lds;
+  first.in = reinterpret_cast<int*>(force_lds + 6 * nb);
+  first.lo = 0;
+  first.cnt = n;
+  first.stage(in, info, i, g);
+  __syncthreads();
+  double largest = 0.0;
+#pragma unroll 1
+  for (int s = 0; s < steps; ++s) {
+    // as k_force does at the start of its launch
+    acc = acc + m;
+    if (threadIdx.x == 0) sp.blog[(step0 + s) & (kDriftLog - 1)] = m;
+    const int len = cut_row(len_all, cut, row_cut(acc));
+    TileAll tile;
+    tile.rec = force_lds + (s & 1) * 3 * nb;
+    tile.in = first.in;
+    double d = 0.0;
+    if (i < n) {
+      int jr0 = 0;
+      if (g < sp.max_nb) jr0 = l.nbr[nbr_entry(i, g, sp.max_nb)];
+      d = force_particle<R, MODE, MODEL, WAY, false, PAIRS>(
+          i, g, sp, inst, ppc, pwc, walls, in, ToRecords{force_lds + (~s & 1) * 3 * nb}, info, l,
+          ws, Fo, To, clock, step_rel + s, flags, true, nullptr, nullptr, nullptr, tile, len, jr0,
+          nullptr);
+    }
+    d = wave_max63(d);
+    if ((threadIdx.x & 63) == 63) wave_drift[s & 1][wave] = d > 0.0 ? d : 0.0;
+    __syncthreads();
+    largest = 0.0;
+    for (int w = 0; w < waves; ++w) largest = fmax(largest, wave_drift[s & 1][w]);
+    m = sqrt(largest);
+  }
+  // the state, and the displacement bound as the last of `steps` launches
+  // leaves it
+  if (i < n && g < 3) {
+    double4* to = g == 0 ? out.pos : (g == 1 ? out.vel : out.omg);
+    to[i] = force_lds[(steps & 1) * 3 * nb + 3 * i + g];
+  }
+  const int64_t last = step0 + steps - 1;
+  if (threadIdx.x < kDriftSpread) {
+    sp.brec[bound_slot(last, 1) * kDriftRec + threadIdx.x * kDriftStride] =
+        threadIdx.x == 0 ? (unsigned long long)__double_as_longlong(largest) : 0ull;
+    sp.brec[bound_slot(last, 2) * kDriftRec + threadIdx.x * kDriftStride] = 0ull;
+    if (threadIdx.x == 0) sp.bacc[bound_slot(last, 0)] = acc;
+  }
 }
 
 // Which way a force launch of n particles takes (us per step with an FP64 law,
@@ -2072,6 +2190,48 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
 #undef DEM_LAUNCH
 #undef DEM_LAUNCH_PAIRS
 #undef DEM_LAUNCH_WAY
+  return hipGetLastError();
+}
+
+// Steps of contexts up to kStepsMax particles.  One compute unit does all the
+// work then, so the time grows with the particles, while a launch per step
+// spreads them; us per step, searches included, several steps in a launch / one
+// (an FP64 law, one MI355X): 20 spheres 4.3 / 6.3, 60 in a box 5.2 / 7.3, 128
+// 6.5 / 8.3, 250 10.0 / 10.0.
+hipError_t launch_force_steps(int mode, int precision, const StepParams& sp, const InstDev* inst,
+                              const PairCoef* pp, const PairCoef* pw, const WallDev* walls,
+                              ParticleBufs in, ParticleBufs out, const int* info, NbrList l,
+                              WallSlots ws, double4* F, double4* T, const int64_t* clock,
+                              int64_t step_rel, int steps, const int* flags, int pair_mode,
+                              hipStream_t s) {
+  if (sp.n <= 0 || steps <= 0) return hipSuccess;
+  if (sp.n > kStepsMax || (mode != 0 && mode != 2)) return hipErrorInvalidValue;
+  const int nb = (sp.n + 15) / 16 * 16;  // whole wavefronts of 16 particles
+  const size_t lds = (size_t)nb * (6 * sizeof(double4) + sizeof(int));
+#define DEM_LAUNCH_PAIRS(RT, M, L, PAIRS)                                                         \
+  hipLaunchKernelGGL((k_force_steps<RT, M, L, PAIRS>), dim3(1), dim3(4 * nb), lds, s, sp, inst,   \
+                     pp, pw, walls, in, out, info, l, ws, F, T, clock, step_rel, steps, flags)
+#define DEM_LAUNCH(RT, M, L)                             \
+  do {                                                   \
+    if (pair_mode == 1) DEM_LAUNCH_PAIRS(RT, M, L, 1);   \
+    else if (pair_mode == 2) DEM_LAUNCH_PAIRS(RT, M, L, 2); \
+    else DEM_LAUNCH_PAIRS(RT, M, L, 0);                  \
+  } while (0)
+#define DEM_LAUNCH_MODE(RT, L)           \
+  do {                                   \
+    if (mode == 0) DEM_LAUNCH(RT, 0, L); \
+    else DEM_LAUNCH(RT, 2, L);           \
+  } while (0)
+  if (precision == 0) {
+    if (sp.model == 0) DEM_LAUNCH_MODE(double, 0);
+    else DEM_LAUNCH_MODE(double, 1);
+  } else {
+    if (sp.model == 0) DEM_LAUNCH_MODE(float, 0);
+    else DEM_LAUNCH_MODE(float, 1);
+  }
+#undef DEM_LAUNCH_MODE
+#undef DEM_LAUNCH
+#undef DEM_LAUNCH_PAIRS
   return hipGetLastError();
 }
 
