@@ -97,7 +97,8 @@ typedef struct {
   double characteristic_velocity; /* V of Eq. (linearkn) [m/s], > 0 for the
                                      linear model, ignored otherwise */
   int32_t force_block;       /* threads per force workgroup: 64, 128 or 256;
-                                0 = 256 (results do not depend on it) */
+                                0 = chosen by the number of particles
+                                (results do not depend on it) */
   int32_t reserved2;         /* must be 0 */
 } dem_config;
 

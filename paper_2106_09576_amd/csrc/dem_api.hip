@@ -100,7 +100,7 @@ struct dem_ctx {
   // requests of a commit under way, placed in one allocation (reserve, place_reserved)
   std::vector<std::pair<void**, size_t>> reserved;
   size_t dev_bytes = 0;
-  int force_block = kBlock;  // threads per force workgroup (64, 128, 256)
+  int force_block = 0;  // threads per force workgroup (64, 128, 256; 0: launch_force chooses)
   double cell_factor = 0.0;  // cell edge / d_max of the grids in use
   uint32_t* d_ckey = nullptr;  // cell keys of every grid (GridDev::ckey)
   uint32_t* d_key_cell = nullptr;  // inverse: the cell (key_base + position) of each key
@@ -1760,7 +1760,7 @@ int dem_create(const dem_config* cfg, dem_ctx** out) {
                    prop.gcnArchName);
   dem_ctx* c = new dem_ctx();
   c->cfg = *cfg;
-  c->force_block = cfg->force_block ? cfg->force_block : kBlock;
+  c->force_block = cfg->force_block;
   c->device = dev;
   c->inst.resize((size_t)cfg->n_instances);
   e = hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking);
@@ -2681,7 +2681,7 @@ int dem_autotune(dem_ctx* c, int32_t trial_steps, dem_tuning* out) {
   memset(out, 0, sizeof(*out));
   for (int k = 0; k < 8; ++k) out->schedules[k] = -1;
   if (c->n == 0) {
-    out->force_block = c->force_block;
+    out->force_block = c->force_block ? c->force_block : kBlock;
     out->rebuild_interval = c->cfg.rebuild_interval;
     out->cell_factor = c->cell_factor;
     return DEM_OK;

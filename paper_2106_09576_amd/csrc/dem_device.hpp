@@ -286,6 +286,7 @@ hipError_t launch_search(const InstDev* inst, const StepParams& sp, const Search
 // pair_mode: 1 when the batch is one instance whose particles all have type
 // 0 (every particle pair takes the pair table's first entry), 2 when every
 // particle has type 0 (the first entry of the particle's own row), else 0.
+// block: threads per workgroup (64, 128 or 256; 0: by the number of particles).
 hipError_t launch_force(int mode, int precision, const StepParams& sp, const InstDev* inst,
                         const PairCoef* pp,
                         const PairCoef* pw, const WallDev* walls, ParticleBufs in,

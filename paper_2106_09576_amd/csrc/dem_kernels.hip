@@ -2130,7 +2130,19 @@ k_force_steps(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* _
 // 293 / 276; 4,300,000 in a silo 748 / 770 / 727.  (Before, every launch
 // streamed loads and stores alike: 200,000 47.1, 1,000,000 147.0, 4,300,000
 // 768.)
+//
+// Threads per workgroup, when the caller leaves it open.  Up to 262,144
+// particles every workgroup is in flight at once, and the compute unit that got
+// the most of them ends last: 200,000 particles are 784 workgroups of 256, four
+// for some of the 256 units and three for most, and 3,136 of 64, 13 and 12.
+// Above, larger workgroups find more of their neighbours in their own records.
+// 256 / 128 / 64 threads, us per step with its share of the search: 1,000
+// spheres 11.1 / 10.8 / 10.1; 8,000 12.5 / 12.0 / 12.1; 60,000 18.1 / 17.9 /
+// 17.9; 100,000 21.7 / 22.1 / 21.4; 200,000 in a silo 38.7 / 38.4 / 37.2, in a
+// mesh 43.0 / 42.5 / 41.8; 400,000 53.6 / 52.6 / 53.3; 1,000,000 139.1 / 140.0
+// / 143.4; 4,300,000 742 / 774 / 827.
 constexpr int64_t kFourLanes = 50000, kTwoLanes = 120000;
+constexpr int64_t kSmallBlocks = 262144;
 constexpr int64_t kAllCached = 600000, kStateCached = 1200000;
 
 enum { kWaySmall4, kWaySmall2, kWayCached, kWayMid, kWayLarge };
@@ -2150,6 +2162,7 @@ hipError_t launch_force(int mode, int precision, const StepParams& sp, const Ins
                         const int* flags, const int* xsel, const double4* Fx, const double4* Tx,
                         double* pf, int block, int pair_mode, hipStream_t s) {
   if (sp.n <= 0) return hipSuccess;
+  if (block == 0) block = sp.n <= kSmallBlocks ? 64 : kBlock;
   if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
   const int way = pf ? kWayMid : force_way(sp.n);  // the record has one instantiation
   const int per_block = way == kWaySmall4 ? block / 4 : (way == kWaySmall2 ? block / 2 : block);
