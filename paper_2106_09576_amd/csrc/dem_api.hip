@@ -405,8 +405,8 @@ int enqueue_rebuild(dem_ctx* c, int check_guard, int move_forces, int64_t step_r
                         move_forces ? c->T[p] : nullptr, c->F[p ^ 1], c->T[p ^ 1],
                         c->d_clock, step_rel, bound_step_rel, c->d_flags, s));
   HIPCHK(launch_search(c->d_inst, c->sp, c->d_blocks, c->n_blocks, c->d_occupied, c->pos[a ^ 1],
-                       c->info[p ^ 1], c->d_cse, c->start, c->perm, c->inv, nlist(c, p), nlist(c, p ^ 1),
-                       c->d_flags, s));
+                       c->info[p ^ 1], c->d_cse, c->start, c->perm, c->inv, nlist(c, p),
+                       nlist(c, p ^ 1), c->d_flags, s));
   c->cur ^= 1;
   c->pcur ^= 1;
   c->n_rebuilds += 1;
@@ -966,10 +966,13 @@ int copy_contacts(dem_ctx* c, int64_t total, const ContactsOut& o, int64_t* pair
   return finish(c);
 }
 
+// The number of contacts.  Places are 32 bits: 2^31 pairs are 2^32 entries, 240
+// GB of lists, all of them full; a sum beyond shows as a negative number.
 int read_total(dem_ctx* c, const int* word, int64_t* total) {
   int v = 0;
   HIPCHK(hipMemcpyAsync(&v, word, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
+  if (v < 0) return set_err(DEM_EINVAL, "more than 2^31 - 1 contacts");
   *total = v;
   return DEM_OK;
 }
@@ -978,9 +981,6 @@ int read_total(dem_ctx* c, const int* word, int64_t* total) {
 // doubles hold for their entries, into host arrays.
 int contacts_to_host(dem_ctx* c, int32_t instance, int64_t cap, const double* planes,
                      int64_t* pairs, double* values, uint8_t* touching, int64_t* n_out) {
-  if (c->cap >= ((int64_t)1 << 32))
-    return set_err(DEM_EINVAL, "%lld list entries: too many for 32-bit pair offsets",
-                   (long long)c->cap);
   const Instance& In = c->inst[(size_t)instance];
   const int L = c->pcur;
   int64_t total = 0;
@@ -1014,8 +1014,8 @@ int commit(dem_ctx* c);
 // the cell of a particle centre lists every triangle that can be its
 // candidate.  kMeshPad, in cells, stands for the rounding of a position in the
 // moving mesh (1e-16 of the coordinates).  A whole cell in its place listed
-// every triangle in more than five times as many cells.  Sets the mesh fields of the
-// instances' walls.
+// every triangle in more than five times as many cells.  Sets the mesh fields
+// of the instances' walls.
 constexpr double kMeshPad = 1.0 / 64.0;
 
 int build_meshes(dem_ctx* c, std::vector<TriDev>* htri, std::vector<int>* hcell,

@@ -11,16 +11,18 @@
 //   walls            Sec. 2.1 last paragraph: same law against a wall
 //   integration      Sec. 2.2: Eqs. (integ_EE), (halfstep), (newvv)
 //
-// Design (MI355X): one thread per particle everywhere.  The force kernel is a
-// gather over each particle's full neighbour row, so every particle sums its
-// own forces in a fixed order (deterministic, no atomics).  Both directions of
+// Design (MI355X): a thread per particle, or several where a launch of one each
+// leaves the chip idle (the force kernel of small contexts, the mesh kernels).
+// The force kernel is a gather over each particle's full neighbour row, so every
+// particle sums its own forces in a fixed order (deterministic, no atomics).  Both directions of
 // a pair keep their own copy of the tangential overlap; the contact law is
 // written so that evaluating it from j's side gives exactly -F and -delta_t
 // (IEEE negation symmetry; this file is compiled without FP contraction), so
 // the two copies never drift apart.  Rows are stored column-major inside each
 // wavefront's slab, so every load of a neighbour index or history component is
 // one coalesced 64-lane access.  The force kernel also integrates its own
-// particle (ping-pong state buffers), so a time step is one launch.
+// particle (ping-pong state buffers), so a time step is one launch, and for a
+// context that one workgroup holds all steps between two searches are.
 #include "dem_device.hpp"
 
 #include <algorithm>
@@ -2020,9 +2022,9 @@ k_force(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* __restr
   __syncthreads();
   double d = 0.0;
   if (i < sp.n)
-    d = force_particle<R, MODE, MODEL, WAY, REC, PAIRS>(i, g, sp, inst, ppc, pwc, walls, in,
-                                                  ToBufs<WAY::kStateNt>{out}, info, l, ws, Fo, To, clock, step_rel, flags,
-                                                  MODE != 1, xsel, Fx, Tx, tile, len, jr0, pf);
+    d = force_particle<R, MODE, MODEL, WAY, REC, PAIRS>(
+        i, g, sp, inst, ppc, pwc, walls, in, ToBufs<WAY::kStateNt>{out}, info, l, ws, Fo, To, clock,
+        step_rel, flags, MODE != 1, xsel, Fx, Tx, tile, len, jr0, pf);
   // this launch's own update produced x^(step + 1)
   if (MODE != 1) raise_drift(sp, sp.brec + bound_slot(step, 1) * kDriftRec, d);
 }
@@ -2126,10 +2128,10 @@ k_force_steps(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* _
 // either, the histories are the ones to stay between their load and their
 // store (WayLarge).  Cached / mid / large: 200,000 41.8 / 46.5 / -; 300,000
 // 46.1 / 54.3 / 56.4; 600,000 91.3 / 91.4 / -; 700,000 108.6 / 99.5 / 105.6;
-// 1,000,000 149.6 / 137.8 / 145.1; 1,250,000 - / 176.7 / 175.1; 1,400,000 211 / 208 / 206; 2,000,000 286 /
-// 293 / 276; 4,300,000 in a silo 748 / 770 / 727.  (Before, every launch
-// streamed loads and stores alike: 200,000 47.1, 1,000,000 147.0, 4,300,000
-// 768.)
+// 1,000,000 149.6 / 137.8 / 145.1; 1,250,000 - / 176.7 / 175.1; 1,400,000 211 /
+// 208 / 206; 2,000,000 286 / 293 / 276; 4,300,000 in a silo 748 / 770 / 727.
+// (Before, every launch streamed loads and stores alike: 200,000 47.1, 1,000,000
+// 147.0, 4,300,000 768.)
 //
 // Threads per workgroup, when the caller leaves it open.  Up to 262,144
 // particles every workgroup is in flight at once, and the compute unit that got
