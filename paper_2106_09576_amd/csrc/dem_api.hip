@@ -1201,7 +1201,12 @@ int plan_grids(dem_ctx* c, double cf, int64_t* total_keys_out, size_t* ckey_tota
 // fraction 0.6, from the mean particle volume and the cell volume.  Equal
 // spheres of diameter d with cells of 1.3 d have 2.5 particles to a cell: 4 x 4
 // x 4 cells, 540 particles to a region; log-normal spheres of 2 to 3.5 mm have
-// 6.7: 4 x 4 x 2 cells, 960 to a region.
+// 6.7: 4 x 4 x 2 cells, 960 to a region.  A block of 4 x 4 x 4 leaves an eighth
+// of the stage free: small spheres that gather in places, and overlaps, fill
+// regions beyond the mean, and those go the slow way.  A settled silo of
+// 200,000 spheres of 2 to 3 mm (903 to a region of 4 x 4 x 4): a search takes 252
+// us, with half the block 163; as a loose bed 149 and 151.  A second halving
+// costs more than that: 4.3M log-normal spheres 2.40 and 3.02 ms.
 void plan_search_blocks(dem_ctx* c) {
   double per_cell = 0.0, row = 0.0;
   for (const Instance& I : c->inst) {
@@ -1220,8 +1225,8 @@ void plan_search_blocks(dem_ctx* c) {
   const int shapes[4][3] = {{2, 2, 2}, {2, 2, 1}, {2, 1, 1}, {1, 1, 1}};
   for (const auto& s : shapes) {
     for (int a = 0; a < 3; ++a) c->sp.sb_bits[a] = s[a];
-    if (per_cell * ((1 << s[0]) + 2) * ((1 << s[1]) + 2) * ((1 << s[2]) + 2) <= kSearchRegion)
-      break;
+    const double room = s[2] == 2 ? 0.875 * kSearchRegion : (double)kSearchRegion;
+    if (per_cell * ((1 << s[0]) + 2) * ((1 << s[1]) + 2) * ((1 << s[2]) + 2) <= room) break;
   }
 }
 
