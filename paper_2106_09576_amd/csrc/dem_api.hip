@@ -403,7 +403,8 @@ int enqueue_rebuild(dem_ctx* c, int check_guard, int move_forces, int64_t step_r
                         c->d_walls, mtables(c), mslots(c, p), mslots(c, p ^ 1), c->rank,
                         move_forces ? c->F[p] : nullptr,
                         move_forces ? c->T[p] : nullptr, c->F[p ^ 1], c->T[p ^ 1],
-                        c->d_clock, step_rel, bound_step_rel, c->d_flags, s));
+                        c->d_clock, step_rel, bound_step_rel, c->d_occupied + c->n_blocks,
+                        c->d_flags, s));
   HIPCHK(launch_search(c->d_inst, c->sp, c->d_blocks, c->n_blocks, c->d_occupied, c->pos[a ^ 1],
                        c->info[p ^ 1], c->d_cse, c->start, c->perm, c->inv, nlist(c, p),
                        nlist(c, p ^ 1), c->d_flags, s));
@@ -1226,7 +1227,8 @@ void plan_search_blocks(dem_ctx* c) {
   for (const auto& s : shapes) {
     for (int a = 0; a < 3; ++a) c->sp.sb_bits[a] = s[a];
     const double room = s[2] == 2 ? 0.875 * kSearchRegion : (double)kSearchRegion;
-    if (per_cell * ((1 << s[0]) + 2) * ((1 << s[1]) + 2) * ((1 << s[2]) + 2) <= room) break;
+    c->sp.sb_fits = per_cell * ((1 << s[0]) + 2) * ((1 << s[1]) + 2) * ((1 << s[2]) + 2) <= room;
+    if (c->sp.sb_fits) break;
   }
 }
 

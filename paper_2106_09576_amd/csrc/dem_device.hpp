@@ -136,6 +136,44 @@ struct SearchBlock {
   int ncell, inst, x, y, z;
 };
 
+// How a contact search finds its rows (us per search of one MI355X: launches,
+// sort and row finishing included).
+//   kSearchBlocks  a workgroup for every block of cells
+//   kSearchListed  the occupied blocks are listed first; a workgroup for each of
+//                  them, or, where they hold fewer than kBlockMin particles on
+//                  average (known on the device only), a thread per particle
+//   kSearchEach    a thread per particle
+//
+// Up to kListedBlocks blocks a launch for all of them takes no longer than a list
+// would.  A thread per particle is the better one where blocks hold few
+// particles: equal spheres in blocks of 4 x 4 x 4 cells, 1,000,000 at a packing of
+// 0.2 (54 to a block) 270 by blocks and 240 each, at 0.25 (68) 298 and 288, at
+// 0.3 (81) 304 and 321, at 0.5 (130) 345 and 461; at 0.01 (2.7) 1,650 and 590.
+// Where the domain has more than one block for two particles, the list costs
+// what the blocks could gain: 1,000,000 at a packing of 0.001 7,010 with a list,
+// 2,830 without, and dense in a corner of a domain of 216 times their volume
+// 1,795 and 1,646.  Where not even the smallest block's region fits the stage in a
+// dense bed, nearly all rows would be found without it: 1,000,000 in cells of
+// 3 d 1,415 and 1,050, 284,000 small spheres among large ones 3,390 and 2,120;
+// contexts of few blocks keep them while the mean region fits (1,000 loose
+// spheres 50 and 88).
+constexpr int kListedBlocks = 2048;
+constexpr int kBlockMin = 64;
+enum { kSearchBlocks, kSearchListed, kSearchEach };
+inline int search_way(int64_t n, int64_t n_blocks, bool fits) {
+  // (eight cells to the smallest block, 64 to its region)
+  if (!fits && (n_blocks > kListedBlocks || n > n_blocks * (kSearchRegion / 8))) return kSearchEach;
+  if (n_blocks <= kListedBlocks) return kSearchBlocks;
+  return 2 * n_blocks <= n ? kSearchListed : kSearchEach;
+}
+// Workgroups of a search by blocks.  With a list there are n / kBlockMin blocks
+// to go through at most, so that their number does not grow with the domain
+// and their threads stay below the 2^32 of a launch.
+inline unsigned search_workgroups(int64_t n, int64_t n_blocks, int way) {
+  const int64_t most = n / kBlockMin;
+  return (unsigned)(way == kSearchListed && most < n_blocks ? most : n_blocks);
+}
+
 // One independent simulation of a batch.  Its cells use the global keys
 // [key_base, key_base + grid.n_keys); its walls are walls[wall_begin,
 // wall_end); its material-pair constants start at coef_base in the tables.
@@ -161,6 +199,7 @@ struct StepParams {
   int model;       // 0 nonlinear (Hertz-Mindlin), 1 linear spring-dashpot
   uint32_t n_keys; // total cell keys; key n_keys collects inactive particles
   int sb_bits[3];  // search block: 2^sb_bits cells along each axis
+  bool sb_fits;    // its region fits the search's LDS stage in a dense bed
   int list_cap;    // candidates past the search's pretest kept per particle in LDS
   int row_cap;     // entries of a row sorted in LDS
   int drift_words; // words of a drift record in use (a power of two <= kDriftSpread)
@@ -255,7 +294,7 @@ hipError_t launch_sort_small(const InstDev* inst, const StepParams& sp, const do
 // It also restarts the displacement bound (StepParams) for the force
 // evaluation at step *clock + bound_step_rel.
 // near_list: n words of scratch for contexts with meshes, whose two counts
-// (MeshSlots::list) are to be zero.
+// (MeshSlots::list) are to be zero.  *n_occupied is set to zero (launch_search).
 hipError_t launch_reorder(const StepParams& sp, const InstDev* inst, const int* perm, int* inv,
                           ParticleBufs src,
                           ParticleBufs dst, const int* gid_src, int* gid_dst,
@@ -264,11 +303,11 @@ hipError_t launch_reorder(const StepParams& sp, const InstDev* inst, const int* 
                           MeshTables mt, MeshSlots ms_src, MeshSlots ms_dst, int* near_list,
                           const double4* F_src, const double4* T_src, double4* F_dst,
                           double4* T_dst, const int64_t* clock, int64_t step_rel,
-                          int64_t bound_step_rel, int* flags, hipStream_t s);
+                          int64_t bound_step_rel, int* n_occupied, int* flags, hipStream_t s);
 // cse: (start, end) of every cell in sorted order, indexed by the cell's
 // position (key_base + (cz * nc[1] + cy) * nc[0] + cx); start: of every key;
 // blocks: the search blocks of all instances in key order; occupied: n_blocks +
-// 1 words of scratch
+// 1 words of scratch, the last of them zero
 hipError_t launch_search(const InstDev* inst, const StepParams& sp, const SearchBlock* blocks,
                          int n_blocks, int* occupied, const double4* pos, const int* info,
                          const int2* cse, const int* start, const int* perm, const int* inv,

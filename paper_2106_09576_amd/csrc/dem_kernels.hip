@@ -628,14 +628,18 @@ __global__ void k_reorder(StepParams sp, const InstDev* __restrict__ inst,
                           const double4* __restrict__ F_src, const double4* __restrict__ T_src,
                           double4* __restrict__ F_dst, double4* __restrict__ T_dst,
                           const int64_t* __restrict__ clock, int64_t step_rel,
-                          int64_t bound_step_rel, int* __restrict__ flags) {
+                          int64_t bound_step_rel, int* __restrict__ n_occupied,
+                          int* __restrict__ flags) {
   int p = xcd_block() * kBlock + threadIdx.x;
   const int n = sp.n;
   if (blockIdx.x == 0 && threadIdx.x < kDriftSpread) {
     // the positions of the next force evaluation are where this search sees them
     const int r = bound_slot(*clock + bound_step_rel, 0);
     sp.brec[r * kDriftRec + threadIdx.x * kDriftStride] = 0ull;
-    if (threadIdx.x == 0) sp.bacc[bound_slot(*clock + bound_step_rel, -1)] = 0.0;
+    if (threadIdx.x == 0) {
+      sp.bacc[bound_slot(*clock + bound_step_rel, -1)] = 0.0;
+      *n_occupied = 0;  // (k_occupied counts)
+    }
   }
   if (p >= n) return;
   const double t = (double)(*clock + step_rel) * sp.dt;  // walls where they are now
@@ -795,12 +799,12 @@ hipError_t launch_reorder(const StepParams& sp, const InstDev* inst, const int* 
                           MeshTables mt, MeshSlots ms_src, MeshSlots ms_dst, int* near_list,
                           const double4* F_src, const double4* T_src, double4* F_dst,
                           double4* T_dst, const int64_t* clock, int64_t step_rel,
-                          int64_t bound_step_rel, int* flags, hipStream_t s) {
+                          int64_t bound_step_rel, int* n_occupied, int* flags, hipStream_t s) {
   hipLaunchKernelGGL(k_reorder, dim3(grid_for(sp.n)), dim3(kBlock), 0, s, sp, inst, perm, inv,
                      src, dst,
                      gid_src, gid_dst, info_src, info_dst, xref, ws_src, ws_dst, walls, mt, ms_dst,
                      near_list, F_src, T_src, F_dst, T_dst, clock, step_rel, bound_step_rel,
-                     flags);
+                     n_occupied, flags);
   if (mt.tri)
     hipLaunchKernelGGL(k_mesh_find, dim3(mesh_grid(sp.n)), dim3(kBlock), 0, s, sp, inst, perm,
                        near_list, dst.pos, info_dst, walls, mt, ms_src, ms_dst, clock, step_rel,
@@ -856,7 +860,9 @@ struct BuildRow {
 // candidates, are then tested on their FP64 positions, in the order found.
 // Bound by the latency of LDS and of those positions; a workgroup per occupied
 // block spreads the work best (workgroups that go through several blocks took
-// twice as long, the occupied blocks being unevenly spread).
+// twice as long, the occupied blocks being unevenly spread).  Where blocks hold
+// too few particles for a workgroup, each particle's 27 cells are read by a
+// thread of its own (search_way).
 //
 // The rows come out in the order of a scan of the 27 cells (z, y, x).  A
 // second kernel puts the pairs that touch now at the front (during the next
@@ -882,7 +888,9 @@ struct RegionTile {
 // the staged region (used where the region does not fit in LDS, or where the
 // FP32 pretest let more through than its list holds).  Returns the number of
 // pairs, of which the first max_nb are stored.
-__device__ __forceinline__ int scan_cells(const InstDev& I, const double4* __restrict__ pos,
+// held: positions of the particles [h0, h0 + n_held).
+__device__ __forceinline__ int scan_cells(const InstDev& I, const double4* held, int h0,
+                                          int n_held, const double4* __restrict__ pos,
                                           const int2* __restrict__ cse, int* __restrict__ nbr,
                                           int p, int max_nb, const double4 pp, int cx, int cy,
                                           int cz) {
@@ -897,7 +905,7 @@ __device__ __forceinline__ int scan_cells(const InstDev& I, const double4* __res
         const int2 se = crow[x];
         for (int q = se.x; q < se.y; ++q) {
           if (q == p) continue;
-          const double4 pq = pos[q];
+          const double4 pq = (unsigned)(q - h0) < (unsigned)n_held ? held[q - h0] : pos[q];
           const double dx = pq.x - pp.x, dy = pq.y - pp.y, dz = pq.z - pp.z;
           const double d2 = (dx * dx + dy * dy) + dz * dz;
           if (!(d2 < I.rs2)) continue;
@@ -909,6 +917,17 @@ __device__ __forceinline__ int scan_cells(const InstDev& I, const double4* __res
       }
     }
   return len;
+}
+
+// The length of the row found for particle p; with more than max_nb pairs the
+// row is incomplete and the step fails (marked by the sign for k_finish_rows).
+__device__ __forceinline__ void store_len(const StepParams& sp, const NbrList& l, int p, int len,
+                                          int* __restrict__ flags) {
+  if (len > sp.max_nb) {
+    atomicOr(flags, kFlagNbrOverflow);
+    len = -sp.max_nb;
+  }
+  l.rowlen[p] = len;
 }
 
 // Row of particle p through the staged region: the candidates within near2
@@ -969,23 +988,67 @@ __device__ __forceinline__ int scan_region(const InstDev& I, const RegionTile& t
 }
 
 // Occupied search blocks (in any order: no result depends on it) and their
-// number.
+// number, with one atomic to a workgroup.
 __global__ void k_occupied(const SearchBlock* __restrict__ blocks, int n_blocks,
                            const int* __restrict__ start, int* __restrict__ list,
                            int* __restrict__ count) {
-  const int b = blockIdx.x * kBlock + threadIdx.x;
+  __shared__ int sh[4], first;
+  const int b = (int)blockIdx.x * kBlock + (int)threadIdx.x;
   bool full = false;
   if (b < n_blocks) full = start[blocks[b].key] < start[blocks[b].key + blocks[b].ncell];
-  const unsigned long long m = __builtin_amdgcn_ballot_w64(full);
-  const int lane = threadIdx.x & 63;
-  int at = 0;
-  if (lane == 0 && m) at = atomicAdd(count, __popcll(m));
-  at = __shfl(at, 0, 64);
-  if (full) list[at + __popcll(m & ((1ull << lane) - 1ull))] = b;
+  int total;
+  const int at = block_exclusive_scan(full ? 1 : 0, sh, &total);
+  if (threadIdx.x == 0 && total > 0) first = atomicAdd(count, total);
+  __syncthreads();
+  if (full) list[first + at] = b;
 }
 
-// One workgroup per occupied block (with a list: blocks list[0 .. *count); the
-// grid then has a workgroup for every block, and those left over end at once).
+// Whether a search with a list of the occupied blocks goes by blocks: where
+// these hold fewer than kBlockMin particles on average the rows are taken one
+// thread per sorted particle instead, since the time of a workgroup is that of
+// its region (up to 216 cell ranges), whatever the block holds.
+__device__ __forceinline__ bool by_blocks(const int* __restrict__ count, int n_active) {
+  return (int64_t)*count * kBlockMin <= n_active;
+}
+
+// Every row, one thread per sorted particle (with count: unless by_blocks).  The
+// workgroup's positions are staged in LDS: most candidates of particles in
+// spatial order lie among them.  Bound by the latency of the candidates' loads,
+// hence eight wavefronts per SIMD.
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8)))
+k_scan_each(const InstDev* __restrict__ inst, StepParams sp, const int* __restrict__ count,
+            const double4* __restrict__ pos, const int* __restrict__ info,
+            const int2* __restrict__ cse, const int* __restrict__ start, NbrList l,
+            int* __restrict__ flags) {
+  __shared__ double4 held[kBlock];
+  const int n_active = start[sp.n_keys];  // particles in cells: they come first
+  if (count && by_blocks(count, n_active)) return;
+  const int p0 = xcd_block() * kBlock, p = p0 + (int)threadIdx.x;
+  double4 pp = make_double4(0.0, 0.0, 0.0, 0.0);
+  if (p < n_active) held[threadIdx.x] = pp = pos[p];
+  __syncthreads();
+  if (p >= n_active) return;
+  const int n_held = n_active - p0 < kBlock ? n_active - p0 : kBlock;
+  // once for every instance among the wavefront's lanes (nearly always one,
+  // whose table entry then sits in scalar registers)
+  const int b = info[p] >> kInstShift;
+  for (;;) {
+    const int u = __builtin_amdgcn_readfirstlane(b);
+    if (b != u) continue;
+    const InstDev& I = inst[u];
+    const GridDev& g = I.grid;
+    store_len(sp, l, p,
+              scan_cells(I, held, p0, n_held, pos, cse, l.nbr, p, sp.max_nb, pp,
+                         cell_coord(pp.x, g.lo[0], g.h, g.nc[0]),
+                         cell_coord(pp.y, g.lo[1], g.h, g.nc[1]),
+                         cell_coord(pp.z, g.lo[2], g.h, g.nc[2])),
+              flags);
+    return;
+  }
+}
+
+// One workgroup per block, or with a list per occupied block (blocks list[0 ..
+// *count)) if by_blocks.
 // The rows are left in the order found, the gap class in the top bits of each
 // entry, for k_finish_rows.
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6)))
@@ -999,7 +1062,7 @@ k_scan_rows(const InstDev* __restrict__ inst, StepParams sp,
   const int tid = threadIdx.x;
   int b = blockIdx.x;
   if (list) {
-    if (b >= *count) return;
+    if (b >= *count || !by_blocks(count, start[sp.n_keys])) return;
     b = list[b];
   }
   const SearchBlock B = blocks[b];
@@ -1051,13 +1114,9 @@ k_scan_rows(const InstDev* __restrict__ inst, StepParams sp,
                         make_float3((float)((pp.x - o0) * I.ih), (float)((pp.y - o1) * I.ih),
                                     (float)((pp.z - o2) * I.ih)),
                         ((cz - B.z + 1) * r1 + (cy - B.y + 1)) * r0 + (cx - B.x + 1));
-    if (len < 0) len = scan_cells(I, pos, cse, l.nbr, p, sp.max_nb, pp, cx, cy, cz);
-    if (len > sp.max_nb) {
-      // the row is incomplete and the step fails
-      atomicOr(flags, kFlagNbrOverflow);
-      len = -sp.max_nb;
-    }
-    l.rowlen[p] = len;
+    if (len < 0)
+      len = scan_cells(I, nullptr, 0, 0, pos, cse, l.nbr, p, sp.max_nb, pp, cx, cy, cz);
+    store_len(sp, l, p, len, flags);
   }
 }
 
@@ -1209,26 +1268,24 @@ k_finish_rows(int n, int max_nb, const int* __restrict__ info, const int* __rest
   }
 }
 
-// Search blocks above which the occupied ones are listed first: 2,048
-// workgroups are in flight at once, so up to there the empty ones cost nothing
-// that a launch would not.
-constexpr int kListedBlocks = 2048;
-
 hipError_t launch_search(const InstDev* inst, const StepParams& sp, const SearchBlock* blocks,
                          int n_blocks, int* occupied, const double4* pos, const int* info,
                          const int2* cse, const int* start, const int* perm, const int* inv,
                          NbrList old_l, NbrList new_l, int* flags, hipStream_t s) {
   if (sp.n <= 0 || n_blocks <= 0) return hipSuccess;
-  int* list = n_blocks > kListedBlocks ? occupied : nullptr;
-  if (list) {
-    hipError_t e = launch_fill_i32(list + n_blocks, 0, 1, s);
-    if (e != hipSuccess) return e;
+  const int way = search_way(sp.n, n_blocks, sp.sb_fits);
+  int* list = way == kSearchListed ? occupied : nullptr;
+  int* count = list ? list + n_blocks : nullptr;
+  if (list)
     hipLaunchKernelGGL(k_occupied, dim3((unsigned)((n_blocks + kBlock - 1) / kBlock)), dim3(kBlock),
-                       0, s, blocks, n_blocks, start, list, list + n_blocks);
-  }
-  hipLaunchKernelGGL(k_scan_rows, dim3((unsigned)n_blocks), dim3(kBlock),
-                     (size_t)sp.list_cap * kBlock * sizeof(uint16_t), s, inst, sp, blocks, list,
-                     list ? list + n_blocks : nullptr, pos, cse, start, new_l, flags);
+                       0, s, blocks, n_blocks, start, list, count);
+  if (way != kSearchBlocks)
+    hipLaunchKernelGGL(k_scan_each, dim3(grid_for(sp.n)), dim3(kBlock), 0, s, inst, sp, count, pos,
+                       info, cse, start, new_l, flags);
+  if (way != kSearchEach)
+    hipLaunchKernelGGL(k_scan_rows, dim3(search_workgroups(sp.n, n_blocks, way)), dim3(kBlock),
+                       (size_t)sp.list_cap * kBlock * sizeof(uint16_t), s, inst, sp, blocks, list,
+                       count, pos, cse, start, new_l, flags);
   hipLaunchKernelGGL(k_finish_rows, dim3(grid_for(sp.n)), dim3(kBlock),
                      (size_t)sp.row_cap * kBlock * sizeof(unsigned), s, sp.n, sp.max_nb, info,
                      perm, inv, old_l, new_l, sp.row_cap);
