@@ -786,9 +786,10 @@ k_mesh_find(StepParams sp, const InstDev* __restrict__ inst, const int* __restri
 }
 
 // Workgroups of 32 particles each: enough to keep the chip busy, and no more
-// than a context can need.
+// than a context can need (one for a context without particles: a launch has
+// to have one).
 static unsigned mesh_grid(int n) {
-  const int64_t b = ((int64_t)n + 31) / 32;
+  const int64_t b = std::max<int64_t>(((int64_t)n + 31) / 32, 1);
   return (unsigned)(b < 2048 ? b : 2048);
 }
 
