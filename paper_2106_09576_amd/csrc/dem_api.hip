@@ -97,8 +97,9 @@ struct dem_ctx {
 
   std::vector<void*> allocs;
   std::vector<size_t> alloc_bytes;
-  // requests of a commit under way, placed in one allocation (reserve, place_reserved)
+  // requests for one allocation (reserve_t, place_reserved)
   std::vector<std::pair<void**, size_t>> reserved;
+  void* grid_alloc = nullptr;  // the allocation of what depends on the grids (place_grids)
   size_t dev_bytes = 0;
   int force_block = 0;  // threads per force workgroup (64, 128, 256; 0: launch_force chooses)
   double cell_factor = 0.0;  // cell edge / d_max of the grids in use
@@ -200,18 +201,19 @@ int dalloc_t(dem_ctx* c, T** p, size_t count) {
   return dalloc(c, (void**)p, count * sizeof(T));
 }
 
-// A commit's buffers come out of one allocation: some fifty of them cost 3 ms
-// to allocate and 4.7 ms to free one by one, a quarter of building a context
-// of 100,000 spheres.  reserve_t notes a request, place_reserved allocates for
-// all of them and sets their pointers.  They start on 2 MiB boundaries as soon
-// as they are that large, as allocations of their own do.
+// A commit's buffers come out of two allocations, one for what depends on the
+// grids: some fifty of them cost 3 ms to allocate and 4.7 ms to free one by one,
+// a quarter of building a context of 100,000 spheres.  reserve_t notes a request,
+// place_reserved allocates for all of them and sets their pointers.  They start
+// on 2 MiB boundaries as soon as they are that large, as allocations of their own
+// do.
 template <typename T>
 void reserve_t(dem_ctx* c, T** p, size_t count) {
   *p = nullptr;
   c->reserved.emplace_back((void**)p, std::max<size_t>(count * sizeof(T), 256));
 }
 
-int place_reserved(dem_ctx* c) {
+int place_reserved(dem_ctx* c, void** base_out = nullptr) {
   auto aligned = [](size_t at, size_t bytes) {
     const size_t to = bytes >= (2u << 20) ? (2u << 20) : 256;
     return (at + to - 1) / to * to;
@@ -227,11 +229,26 @@ int place_reserved(dem_ctx* c) {
     at += r.second;
   }
   c->reserved.clear();
+  if (base_out) *base_out = base;
   return rc;
 }
 
-// Free one allocation made by dalloc (after the stream has drained); part of a
-// commit's allocation stays until that is freed.
+// The buffers whose sizes follow from the grids, in an allocation of their own:
+// regrid replaces them.
+int place_grids(dem_ctx* c, int64_t n_keys, size_t n_blocks) {
+  const size_t keys = (size_t)std::max<int64_t>(n_keys, 1);
+  reserve_t(c, &c->count, (size_t)n_keys + 1);
+  reserve_t(c, &c->start, (size_t)n_keys + 2);
+  reserve_t(c, &c->tile_sums, (size_t)((n_keys + 1 + 1023) / 1024 + 1));
+  reserve_t(c, &c->d_ckey, keys);
+  reserve_t(c, &c->d_key_cell, keys);
+  reserve_t(c, &c->d_cse, keys);
+  reserve_t(c, &c->d_blocks, std::max<size_t>(n_blocks, 1));
+  reserve_t(c, &c->d_occupied, n_blocks + 1);
+  return place_reserved(c, &c->grid_alloc);
+}
+
+// Free one allocation made by dalloc (after the stream has drained).
 void dfree(dem_ctx* c, void* p) {
   if (!p) return;
   for (size_t k = 0; k < c->allocs.size(); ++k)
@@ -270,6 +287,7 @@ void free_particles(dem_ctx* c) {
   c->allocs.clear();
   c->alloc_bytes.clear();
   c->dev_bytes = 0;
+  c->grid_alloc = nullptr;
   c->d_ckey = nullptr;
   c->d_key_cell = nullptr;
   c->d_cse = nullptr;
@@ -1152,7 +1170,7 @@ double wall_rate(const dem_ctx* c) {
 // never below the search radius r_s: cell counts and one key range per
 // instance.  The instances keep their previous grids when the new ones would
 // not fit.
-int plan_grids(dem_ctx* c, double cf, int64_t* total_keys_out, size_t* ckey_total_out) {
+int plan_grids(dem_ctx* c, double cf, int64_t* total_keys_out) {
   const int B = (int)c->inst.size();
   std::vector<GridDev> grids((size_t)B);
   std::vector<uint32_t> bases((size_t)B);
@@ -1193,7 +1211,6 @@ int plan_grids(dem_ctx* c, double cf, int64_t* total_keys_out, size_t* ckey_tota
   }
   c->cell_factor = cf;
   *total_keys_out = total_keys;
-  *ckey_total_out = (size_t)total_keys;
   return DEM_OK;
 }
 
@@ -1347,47 +1364,23 @@ void point_grids(dem_ctx* c, std::vector<InstDev>* hinst) {
 // cells (histories are carried as at every search).
 int regrid(dem_ctx* c, double cf) {
   int64_t total_keys = 0;
-  size_t ckey_total = 0;
-  int rc = plan_grids(c, cf, &total_keys, &ckey_total);
+  int rc = plan_grids(c, cf, &total_keys);
   if (rc) return rc;
   destroy_graphs(c);
   HIPCHK(hipStreamSynchronize(c->stream));
-  dfree(c, c->count);
-  dfree(c, c->start);
-  dfree(c, c->tile_sums);
-  dfree(c, c->d_ckey);
-  dfree(c, c->d_key_cell);
-  dfree(c, c->d_cse);
-  dfree(c, c->d_blocks);
-  dfree(c, c->d_occupied);
-  c->d_blocks = nullptr;
-  c->d_occupied = nullptr;
-  c->count = c->start = c->tile_sums = nullptr;
-  c->d_ckey = c->d_key_cell = nullptr;
-  c->d_cse = nullptr;
-  rc = rc ? rc : dalloc_t(c, &c->count, (size_t)total_keys + 1);
-  rc = rc ? rc : dalloc_t(c, &c->start, (size_t)total_keys + 2);
-  rc = rc ? rc : dalloc_t(c, &c->tile_sums, (size_t)((total_keys + 1 + 1023) / 1024 + 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_ckey, std::max<size_t>(ckey_total, 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_key_cell, std::max<size_t>(ckey_total, 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_cse, std::max<size_t>(ckey_total, 1));
-  if (rc) {
-    c->failed = true;
-    return rc;
-  }
   std::vector<uint32_t> hckey, hkeycell;
   std::vector<InstDev> hinst;
   std::vector<SearchBlock> hblocks;
   plan_search_blocks(c);
   grid_tables(c, &hckey, &hkeycell, &hinst, &hblocks);
-  point_grids(c, &hinst);
   c->n_blocks = (int)hblocks.size();
-  rc = dalloc_t(c, &c->d_blocks, std::max<size_t>(hblocks.size(), 1));
-  rc = rc ? rc : dalloc_t(c, &c->d_occupied, hblocks.size() + 1);
+  dfree(c, c->grid_alloc);
+  rc = place_grids(c, total_keys, hblocks.size());
   if (rc) {
     c->failed = true;
     return rc;
   }
+  point_grids(c, &hinst);
   if (!hckey.empty()) {
     HIPCHK(hipMemcpyAsync(c->d_blocks, hblocks.data(), hblocks.size() * sizeof(SearchBlock),
                           hipMemcpyHostToDevice, c->stream));
@@ -1430,7 +1423,6 @@ int commit(dem_ctx* c) {
   const double f = std::min(c->cfg.neighbor_threshold, c->cfg.cell_factor);
   int64_t total_keys = 0;
   double bound_nb = 16.0;
-  size_t ckey_total = 0;
   int n_walls = 0;
   for (int b = 0; b < B; ++b) {
     Instance& I = c->inst[(size_t)b];
@@ -1453,7 +1445,7 @@ int commit(dem_ctx* c) {
     n_walls += (int)I.walls.size();
   }
   {
-    int rc = plan_grids(c, c->cfg.cell_factor, &total_keys, &ckey_total);
+    int rc = plan_grids(c, c->cfg.cell_factor, &total_keys);
     if (rc) return rc;
   }
   std::vector<TriDev> htri;
@@ -1545,9 +1537,6 @@ int commit(dem_ctx* c) {
   reserve_t(c, &c->xref, NN);
   reserve_t(c, &c->keys, NN);
   reserve_t(c, &c->rank, NN);
-  reserve_t(c, &c->count, (size_t)total_keys + 1);
-  reserve_t(c, &c->start, (size_t)total_keys + 2);
-  reserve_t(c, &c->tile_sums, (size_t)((total_keys + 1 + 1023) / 1024 + 1));
   reserve_t(c, &c->perm0, NN);
   reserve_t(c, &c->perm, NN);
   reserve_t(c, &c->inv, NN);
@@ -1558,9 +1547,6 @@ int commit(dem_ctx* c) {
   reserve_t(c, &c->d_flags, 1);
   reserve_t(c, &c->d_clock, 1);
   reserve_t(c, &c->d_stats, 4);
-  reserve_t(c, &c->d_ckey, std::max<size_t>(ckey_total, 1));
-  reserve_t(c, &c->d_key_cell, std::max<size_t>(ckey_total, 1));
-  reserve_t(c, &c->d_cse, std::max<size_t>(ckey_total, 1));
   reserve_t(c, &c->d_bound, (size_t)kBoundWords);
   if (!htri.empty()) {
     reserve_t(c, &c->d_tri, htri.size());
@@ -1574,9 +1560,8 @@ int commit(dem_ctx* c) {
     reserve_t(c, &c->Fm, NN);
     reserve_t(c, &c->Tm, NN);
   }
-  reserve_t(c, &c->d_blocks, std::max<size_t>(hblocks.size(), 1));
-  reserve_t(c, &c->d_occupied, hblocks.size() + 1);
   int rc = place_reserved(c);
+  rc = rc ? rc : place_grids(c, total_keys, hblocks.size());
   // (an allocation of its own: it is freed when the record is disabled)
   if (c->record_pf)
     rc = rc ? rc : dalloc_t(c, &c->pair_force, (size_t)std::max<int64_t>(c->cap, 1) * 3);
