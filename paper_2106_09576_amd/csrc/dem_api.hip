@@ -1234,12 +1234,8 @@ void plan_search_blocks(dem_ctx* c) {
     per_cell = std::max(per_cell, 0.6 * I.h * I.h * I.h * (double)I.n / vol);
     row = std::max(row, 0.6 * 4.0 / 3.0 * kPi * I.rs * I.rs * I.rs * (double)I.n / vol);
   }
-  // what is kept in LDS per particle, from the mean row of such a bed: lists of
-  // 2 bytes an entry that nearly every particle's candidates fit in (those of
-  // the others are found a slower way), rows of 4 bytes an entry that may spill
-  // a little
-  c->sp.list_cap = std::min((int)(1.5 * row) + 1, 88);
-  c->sp.row_cap = std::min({(int)(1.2 * row) + 2, 48, c->max_nb});
+  c->sp.list_cap = list_capacity(row);
+  c->sp.row_cap = row_capacity(row, c->max_nb);
   const int shapes[4][3] = {{2, 2, 2}, {2, 2, 1}, {2, 1, 1}, {1, 1, 1}};
   for (const auto& s : shapes) {
     for (int a = 0; a < 3; ++a) c->sp.sb_bits[a] = s[a];

@@ -174,6 +174,18 @@ inline unsigned search_workgroups(int64_t n, int64_t n_blocks, int way) {
   return (unsigned)(way == kSearchListed && most < n_blocks ? most : n_blocks);
 }
 
+// What a search keeps in LDS per particle, from the mean row of a dense bed:
+// lists of 2 bytes an entry that nearly every particle's candidates fit in (those
+// of the others are found a slower way), rows of 4 bytes an entry that may spill a
+// little.  (A mean row can be anything: a few large spheres among very many small
+// ones.)
+inline int list_capacity(double row) { return row < 58.0 ? (int)(1.5 * row) + 1 : 88; }
+inline int row_capacity(double row, int max_nb) {
+  const int r = row < 40.0 ? (int)(1.2 * row) + 2 : 48;
+  const int most = max_nb < 48 ? max_nb : 48;
+  return r < most ? r : most;
+}
+
 // One independent simulation of a batch.  Its cells use the global keys
 // [key_base, key_base + grid.n_keys); its walls are walls[wall_begin,
 // wall_end); its material-pair constants start at coef_base in the tables.

@@ -1,7 +1,8 @@
 """Launch arithmetic of the contact search (host functions of dem_device.hpp,
 compiled for the CPU): for every number of particles and of search blocks that
 a context can have, the workgroups suffice for the blocks that are gone through
-and their threads stay below the 2^32 of one launch."""
+and their threads stay below the 2^32 of one launch; for every mean row, what a
+workgroup keeps in LDS stays below 64 KB."""
 import os
 import subprocess
 
@@ -35,6 +36,22 @@ int main() {
             }
             ++checked;
           }
+  for (double row = 1e-3; row < 1e300; row *= 1.01) {
+    // 256 lists of 2 bytes an entry beside the region's stage, rows of 4 bytes
+    const int list = list_capacity(row);
+    const double l = 1.5 * row, r = 1.2 * row;
+    if (list < 1 || list != (l < 87.0 ? (int)l + 1 : 88) || 18 * 1024 + 512 * list > 64 * 1024) {
+      std::printf("row %g: list of %d\n", row, list);
+      return 1;
+    }
+    for (int max_nb : {1, 16, 44, 47, 48, 49, 4096}) {
+      const int cap = row_capacity(row, max_nb), want = r < 46.0 ? (int)r + 2 : 48;
+      if (cap != (want < max_nb ? want : max_nb) || cap < 1 || 1024 * cap > 64 * 1024) {
+        std::printf("row %g, %d neighbours: row of %d\n", row, max_nb, cap);
+        return 1;
+      }
+    }
+  }
   std::printf("%ld launches\n", checked);
   return checked > 500 ? 0 : 1;
 }
