@@ -1498,11 +1498,7 @@ int commit(dem_ctx* c) {
   sp.rolling = c->cfg.rolling_model;
   sp.model = c->cfg.contact_model;
   sp.n_keys = (uint32_t)total_keys;
-  // about 64 wavefronts to a word (0.4 us of atomics, one after the other),
-  // one word for the smallest launches, whose lanes then read a single line
-  sp.drift_words = 1;
-  while (sp.drift_words < kDriftSpread && (int64_t)sp.drift_words * 64 * 64 < N)
-    sp.drift_words *= 2;
+  sp.drift_words = drift_words_for(N);
   sp.drift_scale = ihs_min == ihs_max ? c->cfg.dt * ihs_max : 0.0;
 
   // cell-key tables, search blocks and instance table

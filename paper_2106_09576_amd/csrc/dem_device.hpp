@@ -144,8 +144,11 @@ struct SearchBlock {
 //                  average (known on the device only), a thread per particle
 //   kSearchEach    a thread per particle
 //
-// Up to kListedBlocks blocks a launch for all of them takes no longer than a list
-// would.  A thread per particle is the better one where blocks hold few
+// The list and the launch that it makes room for take 4 to 5 us: 30,000 spheres
+// at a packing of 0.5 among 1,000 blocks 87.5 without and 92 with them, among
+// 10,000 91 and 96, 300,000 among 20,000 157 and 157.  Where blocks hold few
+// particles they gain from some 2,000 blocks on: 10,000 spheres among 857 blocks
+// 77 by blocks, 89 each; among 3,906 91 and 85.  A thread per particle is the better one where blocks hold few
 // particles: equal spheres in blocks of 4 x 4 x 4 cells, 1,000,000 at a packing of
 // 0.2 (54 to a block) 270 by blocks and 240 each, at 0.25 (68) 298 and 288, at
 // 0.3 (81) 304 and 321, at 0.5 (130) 345 and 461; at 0.01 (2.7) 1,650 and 590.
@@ -172,6 +175,21 @@ inline int search_way(int64_t n, int64_t n_blocks, bool fits) {
 inline unsigned search_workgroups(int64_t n, int64_t n_blocks, int way) {
   const int64_t most = n / kBlockMin;
   return (unsigned)(way == kSearchListed && most < n_blocks ? most : n_blocks);
+}
+
+// Lanes to a particle in the force kernel of a context of n (force_way).
+constexpr int64_t kFourLanes = 50000, kTwoLanes = 120000;
+inline int force_lanes(int64_t n) { return n <= kFourLanes ? 4 : (n <= kTwoLanes ? 2 : 1); }
+
+// Words of a drift record in use: about 64 wavefronts of a force launch to a word
+// (0.4 us of atomics, one after the other), one word for the smallest launches,
+// whose lanes then read a single line.  Counted by particles instead, 256
+// wavefronts of four lanes to a particle shared a word: 4,096 spheres 9.2 us per
+// step instead of 8.1, 8,000 10.1 and 8.9, 15,600 11.1 and 9.7, 30,000 12.0 and 11.2.
+inline int drift_words_for(int64_t n) {
+  int words = 1;
+  while (words < kDriftSpread && (int64_t)words * 64 * 64 < n * force_lanes(n)) words *= 2;
+  return words;
 }
 
 // What a search keeps in LDS per particle, from the mean row of a dense bed:

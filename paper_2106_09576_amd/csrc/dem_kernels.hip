@@ -2201,15 +2201,13 @@ k_force_steps(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* _
 // 17.9; 100,000 21.7 / 22.1 / 21.4; 200,000 in a silo 38.7 / 38.4 / 37.2, in a
 // mesh 43.0 / 42.5 / 41.8; 400,000 53.6 / 52.6 / 53.3; 1,000,000 139.1 / 140.0
 // / 143.4; 4,300,000 742 / 774 / 827.
-constexpr int64_t kFourLanes = 50000, kTwoLanes = 120000;
 constexpr int64_t kSmallBlocks = 262144;
 constexpr int64_t kAllCached = 600000, kStateCached = 1200000;
 
 enum { kWaySmall4, kWaySmall2, kWayCached, kWayMid, kWayLarge };
 
 static int force_way(int64_t n) {
-  if (n <= kFourLanes) return kWaySmall4;
-  if (n <= kTwoLanes) return kWaySmall2;
+  if (force_lanes(n) > 1) return force_lanes(n) == 4 ? kWaySmall4 : kWaySmall2;
   if (n <= kAllCached) return kWayCached;
   return n <= kStateCached ? kWayMid : kWayLarge;
 }
