@@ -815,13 +815,12 @@ int flags_to_error(dem_ctx* c, int flags) {
                  flags);
 }
 
-// host copy of the current particle arrays in sorted order
+// host copy of the particles' numbers and info words in sorted order
 struct HostSnapshot {
-  std::vector<double4> pos;
   std::vector<int> gid, info;
 };
 
-int snapshot(dem_ctx* c, HostSnapshot& h, bool want_pos) {
+int snapshot(dem_ctx* c, HostSnapshot& h) {
   const size_t n = (size_t)c->n;
   h.gid.resize(n);
   h.info.resize(n);
@@ -829,11 +828,6 @@ int snapshot(dem_ctx* c, HostSnapshot& h, bool want_pos) {
                         c->stream));
   HIPCHK(hipMemcpyAsync(h.info.data(), c->info[c->pcur], n * sizeof(int),
                         hipMemcpyDeviceToHost, c->stream));
-  if (want_pos) {
-    h.pos.resize(n);
-    HIPCHK(hipMemcpyAsync(h.pos.data(), c->pos[c->cur], n * sizeof(double4),
-                          hipMemcpyDeviceToHost, c->stream));
-  }
   HIPCHK(hipStreamSynchronize(c->stream));
   return DEM_OK;
 }
@@ -1958,7 +1952,7 @@ int dem_get_mesh_contacts(dem_ctx* c, int32_t instance, int64_t cap, int64_t* tr
   }
   if (int rc = wait_user(c)) return rc;
   HostSnapshot h;
-  if (int rc = snapshot(c, h, false)) return rc;
+  if (int rc = snapshot(c, h)) return rc;
   const size_t n = (size_t)c->n;
   std::vector<int> tr(n * kMeshSlots);
   std::vector<double> th(n * kMeshSlots * 3);
@@ -2377,7 +2371,7 @@ int dem_restore_mesh_contacts(dem_ctx* c, int32_t instance, int64_t n_tri,
   }
   if (int rc = wait_user(c)) return rc;
   HostSnapshot h;
-  if (int rc = snapshot(c, h, true)) return rc;
+  if (int rc = snapshot(c, h)) return rc;
   const size_t n = (size_t)c->n;
   const int L = c->pcur;
   const Instance& In = c->inst[(size_t)instance];
