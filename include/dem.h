@@ -428,7 +428,10 @@ int dem_autotune(dem_ctx* ctx, int32_t trial_steps, dem_tuning* out);
 /* Benchmark instrumentation.  While enabled, dem_step launches every kernel
    directly (no graphs) and records HIP events around each force launch and
    each contact search; dem_get_timing writes {force ms total, force launches,
-   search ms total, searches} accumulated since dem_set_timing was called. */
+   search ms total, searches} accumulated since dem_set_timing was called.
+   Contexts of up to 128 particles without mesh walls, whose steps between two
+   searches are otherwise one launch, launch every step by itself then (also in
+   dem_autotune's trials of force_block, which such a context does not use). */
 int dem_set_timing(dem_ctx* ctx, int32_t enable);
 int dem_get_timing(dem_ctx* ctx, double* out4);
 

@@ -1660,8 +1660,8 @@ __device__ __forceinline__ void st_own(const double4& v, double4* p) {
 
 // acc[c] += the values v[c] of the G lanes of a particle, lane by lane: lane g
 // of the particle is lane g (64 / G) + its place in the wavefront, so whole
-// rows of 16 lanes (half rows for G = 8) are handed round.  All lanes of the
-// particle get the same sums.
+// rows of 16 lanes are handed round.  All lanes of the particle get the same
+// sums.
 template <int G>
 __device__ __forceinline__ void add_in_order(double* acc, const double* v, int n);
 
@@ -2177,7 +2177,10 @@ k_force_steps(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* _
 // 16.0 / 19.4; 8,000 12.5 / 15.0 / 20.2; 30,000 14.5 / 15.5 / 20.1; 50,000
 // 17.7 / 18.1 / 19.4; 60,000 in a silo 20.6 / 21.3 / 23.5; 100,000 28.0 / 23.9
 // / 25.0; 130,000 - / 27.2 / 27.5; 200,000 - / 44.6 / 41.8.  8 lanes were
-// never the best.
+// never the best.  The lines hold for the FP32 law too: dense beds that rest,
+// FP32 (FP64), 30,000 10.8 / 11.5 / 13.1 (11.2 / 11.8 / 13.9); 50,000 13.9 / 13.7 /
+// 15.4 (14.8 / 14.5 / 16.0); 100,000 20.5 / 16.8 / 18.6 (21.6 / 18.2 / 20.2);
+// 130,000 25.4 / 23.4 / 21.4 (27.1 / 24.6 / 24.1).
 //
 // Streaming.  A step touches about 400 bytes per particle (two copies of the
 // state, histories, row entries), and the memory-side cache holds 256 MB.
@@ -2189,12 +2192,17 @@ k_force_steps(StepParams sp, const InstDev* __restrict__ inst, const PairCoef* _
 // 1,000,000 149.6 / 137.8 / 145.1; 1,250,000 - / 176.7 / 175.1; 1,400,000 211 /
 // 208 / 206; 2,000,000 286 / 293 / 276; 4,300,000 in a silo 748 / 770 / 727.
 // (Before, every launch streamed loads and stores alike: 200,000 47.1, 1,000,000
-// 147.0, 4,300,000 768.)
+// 147.0, 4,300,000 768.)  Beds that rest, FP32 (FP64): 500,000 60.3 / 63.5 / 69.7
+// (62.3 / 66.1 / 71.7); 600,000 82.1 / 79.9 / 85.4 (83.8 / 81.5 / 86.8); 1,000,000
+// 140.9 / 124.6 / 135.5 (142.8 / 129.0 / 137.6); 1,400,000 199.6 / 187.9 / 194.2
+// (201.1 / 190.2 / 197.1); 2,000,000 273.3 / 262.3 / 266.7 (276.3 / 265.5 / 269.6).
+// The upper line is that of beds that move; resting ones would stay with WayMid
+// for 1.5 to 3 % up to 2,000,000.
 //
 // Threads per workgroup, when the caller leaves it open.  Up to 262,144
 // particles every workgroup is in flight at once, and the compute unit that got
 // the most of them ends last: 200,000 particles are 784 workgroups of 256, four
-// for some of the 256 units and three for most, and 3,136 of 64, 13 and 12.
+// for some of the 256 units and three for most, and 3,128 of 64, 13 and 12.
 // Above, larger workgroups find more of their neighbours in their own records.
 // 256 / 128 / 64 threads, us per step with its share of the search: 1,000
 // spheres 11.1 / 10.8 / 10.1; 8,000 12.5 / 12.0 / 12.1; 60,000 18.1 / 17.9 /
