@@ -2264,8 +2264,11 @@ int dem_restore(dem_ctx* c, int32_t instance, int64_t n_pairs, const int64_t* pa
   const DeviceScope on(c->device);
   const int L = c->pcur;
   hipStream_t s = c->stream;
-  // device copies of the arguments and the entries found for them, freed when
-  // the call ends
+  // device copies of the arguments and the entries found for them: in the
+  // histories of the other list, which the next search overwrites, so that a
+  // context that fills the device can be restored; only arguments that do not
+  // fit there (very few neighbours per particle) take memory of their own, freed
+  // when the call ends
   struct Temp {
     void* p = nullptr;
     ~Temp() {
@@ -2275,14 +2278,15 @@ int dem_restore(dem_ctx* c, int32_t instance, int64_t n_pairs, const int64_t* pa
   const size_t force_bytes = 24 * (size_t)In.n;
   size_t bytes = 8 + (size_t)n_pairs * (16 + 24 + 16) + (size_t)n_wall * (16 + 24 + 8) +
                  (force ? force_bytes : 0) + (torque ? force_bytes : 0);
-  {
+  char* at = (char*)c->hist[L ^ 1];
+  if (bytes > 24 * (size_t)c->cap) {
     const hipError_t e = hipMalloc(&temp.p, bytes);
     if (e != hipSuccess) {
       temp.p = nullptr;
       return set_err(DEM_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
     }
+    at = (char*)temp.p;
   }
-  char* at = (char*)temp.p;
   auto take = [&](size_t size) {
     char* p = at;
     at += size;
